@@ -4,8 +4,9 @@
 
 Every compile unit below is compiled to an object in parallel, then linked
 into paper_1810_11066_amd/libbitserial.so.  The kernel instantiation sources
-(conv_fast_inst.hip, conv_pix_inst.hip) are compiled once per unit, each with
-its own -D selection, so that the specialisations compile in parallel.
+(conv_fast_inst.hip, conv_pix_inst.hip, conv_tiled_inst.hip) are compiled once
+per unit, each with its own -D selection, so that the specialisations compile
+in parallel.
 Flags:
   --offload-arch=gfx950          MI355X only
   -ffp-contract=off              the quantizer's product must stay a lone
@@ -34,17 +35,21 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # (source, object name, defines)
 UNITS = ([("api.hip", "api", ()), ("quant_pack.hip", "quant_pack", ()),
-          ("conv.hip", "conv", ()), ("conv_pix.hip", "conv_pix", ())] +
+          ("conv.hip", "conv", ()), ("conv_pix.hip", "conv_pix", ()),
+         ("conv_tiled.hip", "conv_tiled", ())] +
          [("conv_fast_inst.hip", "conv_fast_a%d" % a, ("BS_A=%d" % a,))
           for a in range(1, 5)] +
          [("conv_pix_inst.hip", "conv_pix_a%d" % a,
            ("BS_PIX_FAMILY=0", "BS_A=%d" % a)) for a in range(1, 5)] +
          [("conv_pix_inst.hip", "conv_pix_s%d" % a,
            ("BS_PIX_FAMILY=1", "BS_A=%d" % a)) for a in range(1, 5)] +
-         [("conv_pix_inst.hip", "conv_pix_b", ("BS_PIX_FAMILY=2",))])
+         [("conv_pix_inst.hip", "conv_pix_b", ("BS_PIX_FAMILY=2",))] +
+         [("conv_tiled_inst.hip", "conv_tiled_a%d" % a, ("BS_A=%d" % a,))
+          for a in range(1, 5)])
 # every source file the library is built from (headers included)
 SOURCES = sorted({u[0] for u in UNITS} |
-                 {"bs_internal.h", "conv_fast.h", "conv_pix.h"})
+                 {"bs_internal.h", "conv_fast.h", "conv_pix.h",
+                  "conv_tiled.h"})
 
 CFLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

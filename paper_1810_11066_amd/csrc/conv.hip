@@ -7,7 +7,7 @@
 // Accumulation is in uint32 and wraps; the host rejects any problem whose
 // exact result could leave int32, so the wrapped sum equals the exact result.
 //
-// Three kernel families; the host picks one per call (launch_conv):
+// Four kernel families; the host picks one per call (launch_conv):
 //
 // conv_pix_kernel      "pixels on lanes" (conv_pix.h): lane l owns one output
 //                      pixel and keeps its packed input patch in VGPRs; the
@@ -19,16 +19,18 @@
 //                      output channel oc0 + l, the wave walks groups of P
 //                      output pixels of one row; activation words are uniform
 //                      across the wave (scalar loads), filter words of the
-//                      block's 64 channels are staged once in LDS.  Serves
-//                      the shapes the pixel kernel does not (wide channels,
-//                      oc not a multiple of 4).
+//                      block's 64 channels are staged once in LDS.  Kernel
+//                      mode 2 only: the tiled kernel is faster on its shapes.
+// conv_generic_kernel_tiled  pixels on lanes with a run-time window, stride,
+//                      channel count, bit-widths and encodings
+//                      (conv_tiled.h); serves what the pixel kernel does not.
 // conv_generic_kernel  one output per thread, runtime everything; serves
-//                      every remaining shape.
+//                      every remaining shape (a single image or a filter set
+//                      past 2 GiB) and kernel mode 1.
 //
-// In both fast families the inner loop is one v_and_b32 (SGPR x VGPR) and one
-// accumulating v_bcnt_u32_b32 per word pair, into A+W-1 per-shift
-// accumulators per output; the shift-add (and bipolar correction) runs once
-// per output.
+// In the fast families the inner loop is one v_and_b32 (SGPR x VGPR) and one
+// accumulating v_bcnt_u32_b32 per word pair; the shift-add (and bipolar
+// correction) runs once per output.
 #include <algorithm>
 #include <atomic>
 #include <cstdio>
@@ -38,6 +40,7 @@
 
 #include "conv_fast.h"
 #include "conv_pix.h"
+#include "conv_tiled.h"
 
 namespace bs {
 namespace {
@@ -643,11 +646,12 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
     return hipSuccess;
 }
 
-enum class Family { kPixels, kChannels, kGeneric };
+enum class Family { kPixels, kChannels, kTiled, kGeneric };
 
-// The kernel family a call takes: mode 0 tries pixels-on-lanes, then
-// channels-on-lanes, then generic; 3 and 2 try only their own family before
-// generic; 1 is generic only.
+// The kernel family a call takes: mode 0 tries pixels-on-lanes, then the
+// tiled generic kernel, then the plain one; 3 and 2 try only their own family
+// (pixels- or channels-on-lanes) before the plain generic kernel; 1 is that
+// one only.
 Family choose(const ConvShape& s, int mode, pix::PixKernelFn* pfn,
               pix::PlanInfo* info) {
     if (mode == 0 || mode == 3) {
@@ -655,8 +659,8 @@ Family choose(const ConvShape& s, int mode, pix::PixKernelFn* pfn,
             nullptr)
             return Family::kPixels;
     }
-    if ((mode == 0 || mode == 2) && conv_has_fast_path(s))
-        return Family::kChannels;
+    if (mode == 2 && conv_has_fast_path(s)) return Family::kChannels;
+    if (mode == 0 && tiled::covers(s, false)) return Family::kTiled;
     return Family::kGeneric;
 }
 
@@ -682,6 +686,9 @@ hipError_t launch_conv(const ConvShape& s, const uint32_t* act,
                                           g.cw);
             return launch(fn, grid, dim3(kBlock), lds, st, act, wts, out, g);
         }
+        case Family::kTiled:
+            return tiled::launch_conv(s, act, wts, out, nullptr, device_cus(),
+                                      st);
         case Family::kGeneric:
         default: {
             GenericArgs g;
@@ -695,7 +702,8 @@ hipError_t launch_conv_requant(const ConvShape& s, const uint32_t* act,
                                const uint32_t* wts, uint32_t* out,
                                const Requant& rq, const ConvOptions& opt,
                                hipStream_t st) {
-    // the pixels-on-lanes kernel (modes 0 and 3), else plain loops
+    // the pixels-on-lanes kernel (modes 0 and 3), else the tiled generic
+    // kernel (mode 0), else plain loops
     pix::PlanInfo info{};
     pix::PixKernelFn pfn = nullptr;
     if (opt.mode == 0 || opt.mode == 3)
@@ -705,6 +713,9 @@ hipError_t launch_conv_requant(const ConvShape& s, const uint32_t* act,
         return launch_pix(s, pfn, act, wts, reinterpret_cast<int32_t*>(out),
                           opt.units_per_wave, &rq, st);
     }
+    if (opt.mode == 0 && tiled::covers(s, true))
+        return tiled::launch_conv(s, act, wts, reinterpret_cast<int32_t*>(out),
+                                  &rq, device_cus(), st);
     GenericRequantArgs g;
     g.act = act;
     g.wts = wts;
@@ -872,6 +883,8 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
                             pick_group_pixels(s.ow), cw, grid.x, grid.y,
                             kBlock, lds);
         }
+        case Family::kTiled:
+            return tiled::describe(s, enc, device_cus(), buf, len);
         case Family::kGeneric:
         default: {
             GenericArgs g;

@@ -1,0 +1,154 @@
+"""GPU parity of conv_generic_kernel_tiled, the run-time-shaped kernel of the
+shapes no specialisation covers, against the oracle: every group of planes
+(1-8 bits), chunk width (1-4 words, whole and partial last chunks), channel
+tile and remainder, window, stride and padding, the encodings' corrections,
+waves that share a unit's steps, operands swapped for products of few rows,
+and requantized output."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1810_11066_amd import bitserial as bs
+
+pytestmark = pytest.mark.gpu
+
+SENT32 = 0x7FFFFFFF
+GUARD = 1024
+U, B, S = bs.UNIPOLAR, bs.BIPOLAR, bs.SIGNED
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    assert torch.cuda.is_available(), "GPU parity tests need the MI355X"
+    bs.load_library()
+    bs.bs_set_kernel_mode(0)
+    yield
+    bs.bs_set_kernel_mode(0)
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+class Guarded:
+    def __init__(self, numel):
+        self.n = numel
+        self.buf = torch.full((numel + 2 * GUARD,), SENT32, dtype=torch.int32,
+                              device="cuda")
+        self.t = self.buf[GUARD:GUARD + numel]
+
+    def numpy(self):
+        torch.cuda.synchronize()
+        b = self.buf.cpu()
+        assert bool((b[:GUARD] == SENT32).all()), "write before output"
+        assert bool((b[GUARD + self.n:] == SENT32).all()), "write past output"
+        return b[GUARD:GUARD + self.n].numpy()
+
+
+def operands(oracle, seed, n, h, w, c, oc, kh, kw, s, pad, abits, wbits, aenc,
+             wenc):
+    rng = np.random.default_rng(seed)
+    a = rng.integers(0, 1 << abits, size=(n, h, w, c), dtype=np.uint8)
+    wq = rng.integers(0, 1 << wbits, size=(oc, kh, kw, c), dtype=np.uint8)
+    ap, wp = oracle.pack(a, abits), oracle.pack(wq, wbits)
+    want = oracle.conv2d(oracle.conv_params(n, h, w, c, oc, kh, kw, s, pad,
+                                            abits, wbits, aenc, wenc), ap, wp)
+    p = bs.ConvParams(n, h, w, c, oc, kh, kw, s[0], s[1], pad[0], pad[1],
+                      abits, wbits, aenc, wenc)
+    return ap, wp, want, p
+
+
+def run_conv(oracle, seed, *shape):
+    say("tiled conv", shape)
+    ap, wp, want, p = operands(oracle, seed, *shape)
+    assert bs.bs_conv2d_describe(p).startswith("conv_generic_kernel_tiled")
+    g = Guarded(want.size)
+    bs.bs_conv2d(p, dev(ap.view(np.int32)), dev(wp.view(np.int32)), g.t)
+    assert np.array_equal(g.numpy().reshape(want.shape), want)
+
+
+SHAPES = [
+    # n, h, w, c, oc, (kh, kw), (sh, sw), (ph, pw)
+    (2, 7, 9, 90, 24, (3, 3), (1, 1), (1, 1)),     # 3 words, whole chunks
+    (1, 9, 7, 130, 13, (3, 3), (2, 2), (1, 1)),    # 5 words: 3 + 2
+    (1, 6, 8, 200, 30, (3, 3), (1, 1), (2, 2)),    # 7 words: 4 + 3
+    (1, 11, 5, 64, 18, (5, 5), (1, 1), (2, 2)),    # 2 words
+    (3, 5, 13, 17, 6, (3, 3), (1, 1), (1, 1)),     # 1 word
+    (1, 12, 10, 128, 20, (2, 5), (3, 1), (0, 3)),  # window, stride, pad differ
+    (1, 4, 4, 96, 3, (7, 7), (1, 1), (3, 3)),      # window past the image
+    (1, 9, 9, 352, 33, (1, 1), (1, 1), (0, 0)),    # one tap, 11 words
+    (2, 8, 8, 64, 7, (1, 1), (2, 2), (1, 1)),      # pad 1 around 1x1 windows
+]
+BITS = [(1, 1, U, U), (2, 1, U, B), (1, 2, B, U), (1, 1, B, B), (2, 2, S, U),
+        (2, 3, U, S), (3, 3, S, S), (4, 1, U, U), (1, 4, U, B), (4, 2, B, S),
+        (4, 4, B, B), (5, 3, U, U), (8, 1, S, B), (2, 7, U, S), (6, 6, S, B)]
+
+
+@pytest.mark.parametrize("bits", BITS, ids=lambda b: "A%d%sW%d%s" % (
+    b[0], "ubs"[b[2]], b[1], "ubs"[b[3]]))
+def test_conv_encodings(oracle, bits):
+    """Every shape at one choice of widths and encodings."""
+    abits, wbits, aenc, wenc = bits
+    for i, (n, h, w, c, oc, k, s, pad) in enumerate(SHAPES):
+        spec = bs.ConvParams(n, h, w, c, oc, *k, *s, *pad, *bits)
+        if not bs.bs_conv2d_describe(spec).startswith("conv_generic"):
+            continue        # served by a specialised kernel
+        run_conv(oracle, 100 * i + abits * 9 + wbits, n, h, w, c, oc, *k, s,
+                 pad, *bits)
+
+
+@pytest.mark.parametrize("npix,oc", [
+    (64, 4), (65, 5), (130, 12), (63, 16), (64, 17), (200, 31), (128, 150),
+    (4100, 150), (20000, 40)])
+def test_conv_tiles(oracle, npix, oc):
+    """Pixel groups and channel tiles at their edges, from one unit whose
+    steps are shared to grids that fill the chip with the widest tiles."""
+    for abits, wbits in ((1, 1), (2, 2), (3, 3)):
+        if npix * oc > 10 ** 5 and abits > 1:
+            continue
+        run_conv(oracle, npix + oc, 1, 1, npix, 96, oc, 1, 3, (1, 1), (0, 1),
+                 abits, wbits, U, U)
+
+
+@pytest.mark.parametrize("m", [1, 2, 5, 18, 47, 63, 64])
+@pytest.mark.parametrize("n,k", [(1, 40), (70, 100), (129, 800), (1000, 352)])
+def test_dense_few_rows(oracle, m, n, k):
+    """Matrix products of few rows, both ways round, over the encodings."""
+    for abits, wbits, aenc, wenc in ((1, 1, U, U), (2, 2, U, S), (1, 3, B, U),
+                                     (2, 1, U, B), (1, 1, B, B)):
+        say("dense", m, n, k, abits, wbits, aenc, wenc)
+        rng = np.random.default_rng(m * 1000 + n + k)
+        a = rng.integers(0, 1 << abits, size=(m, k), dtype=np.uint8)
+        wq = rng.integers(0, 1 << wbits, size=(n, k), dtype=np.uint8)
+        ap, wp = oracle.pack(a, abits), oracle.pack(wq, wbits)
+        op = oracle.conv_params(1, 1, m, k, n, 1, 1, 1, 0, abits, wbits, aenc,
+                                wenc)
+        want = oracle.conv2d(op, ap.reshape(1, 1, m, abits, -1),
+                             wp.reshape(n, 1, 1, wbits, -1)).reshape(m, n)
+        g = Guarded(m * n)
+        bs.bs_dense_ex(m, n, k, abits, aenc, wbits, wenc,
+                       dev(ap.view(np.int32)), dev(wp.view(np.int32)), g.t)
+        assert np.array_equal(g.numpy().reshape(m, n), want)
+
+
+@pytest.mark.parametrize("oc", [3, 8, 21, 40, 150])
+@pytest.mark.parametrize("obits", [1, 3, 8])
+def test_requant(oracle, oc, obits):
+    for i, (abits, wbits, aenc, wenc) in enumerate(
+            ((2, 1, U, U), (3, 3, S, S), (1, 1, B, B), (4, 4, U, U))):
+        shape = (2, 9, 7, 96, oc, 3, 3, (1, 1), (1, 1), abits, wbits, aenc,
+                 wenc)
+        say("tiled requant", shape, obits)
+        ap, wp, conv, p = operands(oracle, 7 * oc + i, *shape)
+        scale = ((1 << obits) - 1) / max(1.0, float(abs(conv).max()))
+        want = oracle.pack(oracle.quantize(conv.astype(np.float32), scale,
+                                           obits), obits)
+        g = Guarded(want.size)
+        bs.bs_conv2d_requant(p, dev(ap.view(np.int32)),
+                             dev(wp.view(np.int32)), scale, obits, g.t)
+        got = g.numpy().view(np.uint32)
+        assert np.array_equal(got.reshape(want.shape), want)
