@@ -7,24 +7,26 @@
 
 namespace bs {
 
-// Division of a non-negative int32 by a fixed positive divisor with one
-// 64-bit multiply and a shift: q = (n * m) >> s, m = ceil(2^s / d),
-// s = 32 + ceil(log2 d).  Exact for every n < 2^31 (the rounding error
-// n (m d - 2^s) / (d 2^s) stays below 1/d because m d - 2^s < d <= 2^(s-32)).
+// Division of a non-negative int32 by a fixed positive divisor by one
+// multiply-high, an add and a shift (the round-up method of Granlund and
+// Montgomery, "Division by invariant integers using multiplication", 1994):
+// l = ceil(log2 d), m = floor(2^32 (2^l - d) / d) + 1,
+// n / d = (mulhi(n, m) + n) >> l, exact for n < 2^31, where the sum stays
+// below 2^32.  (A 64-bit product and shift is several quarter-rate
+// instructions more, in code that every wave runs.)
 struct FastDiv {
-    uint64_t m;
+    uint32_t m;
     uint32_t s;
     uint32_t d;
 
     __host__ void init(uint32_t divisor) {
         d = divisor;
-        uint32_t sh = 0;
-        while ((1ull << sh) < divisor) ++sh;
-        s = 32 + sh;
-        m = ((1ull << s) + divisor - 1) / divisor;
+        s = 0;
+        while ((1ull << s) < divisor) ++s;
+        m = (uint32_t)((((1ull << s) - divisor) << 32) / divisor + 1);
     }
     __host__ __device__ __forceinline__ uint32_t div(uint32_t n) const {
-        return (uint32_t)(((uint64_t)n * m) >> s);
+        return ((uint32_t)(((uint64_t)n * m) >> 32) + n) >> s;
     }
 };
 

@@ -443,11 +443,18 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
     if (!live) return;
     const int nks = 1 << g.ks_log2;
     const uint32_t* t = lds + (wv - ks) * kTileWords;
-    auto value = [&](int row, int col) {
-        uint32_t v = 0;
-        for (int k = 0; k < nks; ++k)
-            v += t[k * kTileWords + row * kStride + col];
-        return v;
+    // N consecutive channels of one pixel, summed over the unit's waves
+    auto values = [&](auto& v, int row, int col) __attribute__((always_inline)) {
+        constexpr int N = sizeof(v) / sizeof(v[0]);
+        const uint32_t* e = t + row * kStride + col;
+#pragma unroll
+        for (int o = 0; o < N; ++o) v[o] = e[o];
+#pragma unroll 1
+        for (int k = 1; k < nks; ++k) {
+            e += kTileWords;
+#pragma unroll
+            for (int o = 0; o < N; ++o) v[o] += e[o];
+        }
     };
     const int cols = g.unit_cols;
     if constexpr (REQ) {
@@ -458,11 +465,12 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
             const int k8 = col0 / 8 + b8;
             if (k8 > last) break;
             uint32_t codes[2] = {0, 0};
+            uint32_t v[8];
+            values(v, lane, b8 * 8);
 #pragma unroll
             for (int o = 0; o < 8; ++o) {
                 const uint32_t code = quant_code<false>(
-                    (float)(int32_t)value(lane, b8 * 8 + o), g.out_scale,
-                    g.out_qmax);
+                    (float)(int32_t)v[o], g.out_scale, g.out_qmax);
                 if (8 * k8 + o < g.oc) codes[o >> 2] |= code << (8 * (o & 3));
             }
             if (p >= g.npix) continue;
@@ -485,12 +493,14 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
             // channel rows: 64 consecutive results per store
             const int p = pix0 + lane;
             for (int c = ks; c < cols; c += nks) {
+                uint32_t v[1];
+                values(v, lane, c);
                 const bool in = p < g.npix && col0 + c < g.oc;
                 const uint32_t off =
                     4u * ((uint32_t)(col0 + c) * (uint32_t)g.ch_step +
                           (uint32_t)p);
                 __builtin_amdgcn_raw_buffer_store_b32(
-                    value(lane, c), rout, in ? off : kOutOfRange, 0, 0);
+                    v[0], rout, in ? off : kOutOfRange, 0, 0);
             }
         } else if (g.oc % 4 == 0) {
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -499,9 +509,9 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
             const int q = lane & (nq - 1), pr = lane >> lg;
             for (int r = ks; r < nq; r += nks) {
                 const int rowi = r * (64 >> lg) + pr, p = pix0 + rowi;
-                const u32x4 v = {value(rowi, 4 * q), value(rowi, 4 * q + 1),
-                                 value(rowi, 4 * q + 2),
-                                 value(rowi, 4 * q + 3)};
+                uint32_t x[4];
+                values(x, rowi, 4 * q);
+                const u32x4 v = {x[0], x[1], x[2], x[3]};
                 const bool in = p < g.npix && col0 + 4 * q < g.oc;
                 const uint32_t off =
                     4u * ((uint32_t)p * (uint32_t)g.pix_step +
@@ -514,11 +524,13 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
             const int c = lane & (cols - 1), pr = lane >> lg;
             for (int r = ks; r < cols; r += nks) {
                 const int rowi = r * (64 >> lg) + pr, p = pix0 + rowi;
+                uint32_t v[1];
+                values(v, rowi, c);
                 const bool in = p < g.npix && col0 + c < g.oc;
                 const uint32_t off = 4u * ((uint32_t)p * (uint32_t)g.pix_step +
                                            (uint32_t)(col0 + c));
                 __builtin_amdgcn_raw_buffer_store_b32(
-                    value(rowi, c), rout, in ? off : kOutOfRange, 0, 0);
+                    v[0], rout, in ? off : kOutOfRange, 0, 0);
             }
         }
     }
