@@ -36,7 +36,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # (source, object name, defines)
 UNITS = ([("api.hip", "api", ()), ("quant_pack.hip", "quant_pack", ()),
           ("conv.hip", "conv", ()), ("conv_pix.hip", "conv_pix", ()),
-         ("conv_tiled.hip", "conv_tiled", ())] +
+         ("conv_tiled.hip", "conv_tiled", ()),
+         ("dense_rows.hip", "dense_rows", ())] +
          [("conv_fast_inst.hip", "conv_fast_a%d" % a, ("BS_A=%d" % a,))
           for a in range(1, 5)] +
          [("conv_pix_inst.hip", "conv_pix_a%d" % a,
@@ -49,7 +50,7 @@ UNITS = ([("api.hip", "api", ()), ("quant_pack.hip", "quant_pack", ()),
 # every source file the library is built from (headers included)
 SOURCES = sorted({u[0] for u in UNITS} |
                  {"bs_internal.h", "conv_fast.h", "conv_pix.h",
-                  "conv_tiled.h"})
+                  "conv_tiled.h", "dense_rows.h"})
 
 CFLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -134,6 +134,38 @@ struct ConvShape {
     bool bipolar_w;       // wenc == kBipolar
 };
 
+// ---- operands with run-time widths and encodings --------------------------
+
+// Planes handled together by the kernels with run-time bit-widths: `bits`
+// planes split evenly into groups of at most 4 (5 -> 3 + 2, 8 -> 4 + 4).
+inline int plane_groups(int bits) { return (bits + 3) / 4; }
+inline int group_planes(int bits) {
+    return (bits + plane_groups(bits) - 1) / plane_groups(bits);
+}
+
+// Plane weights +-2^i of a code, 0 past its last plane.
+inline void plane_weights(int bits, int enc, int32_t (&w)[8]) {
+    for (int i = 0; i < 8; ++i) w[i] = i < bits ? 1 << i : 0;
+    if (enc == kSigned) w[bits - 1] = -w[bits - 1];
+}
+
+// The result as cs S + csa SA + csw SW + cn N (S, SA, SW the plane-weighted
+// popcounts of a AND w, a and w; N the in-range channel values), or, for +-1
+// data on both sides (xnor), N - 2 D with D in the place of S.
+struct Encoding {
+    int32_t cs, csa, csw, cn;
+    bool xnor;
+};
+inline Encoding encoding_terms(const ConvShape& s) {
+    if (s.aenc == kBipolar && s.wenc == kBipolar && s.abits == 1 &&
+        s.wbits == 1)
+        return Encoding{-2, 0, 0, 1, true};
+    const int aa = s.aenc == kBipolar ? 2 : 1, aw = s.wenc == kBipolar ? 2 : 1;
+    const int ba = s.aenc == kBipolar ? 1 - (1 << s.abits) : 0;
+    const int bw = s.wenc == kBipolar ? 1 - (1 << s.wbits) : 0;
+    return Encoding{aa * aw, aa * bw, ba * aw, ba * bw, false};
+}
+
 // Kernel selection for a conv call.  mode 0: the fastest applicable kernel;
 // 1: generic only; 2: the channels-on-lanes kernel where it applies; 3: the
 // pixels-on-lanes kernel where it applies (2 and 3 fall back to the generic

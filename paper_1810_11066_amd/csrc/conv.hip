@@ -7,7 +7,7 @@
 // Accumulation is in uint32 and wraps; the host rejects any problem whose
 // exact result could leave int32, so the wrapped sum equals the exact result.
 //
-// Four kernel families; the host picks one per call (launch_conv):
+// Five kernel families; the host picks one per call (launch_conv):
 //
 // conv_pix_kernel      "pixels on lanes" (conv_pix.h): lane l owns one output
 //                      pixel and keeps its packed input patch in VGPRs; the
@@ -24,6 +24,8 @@
 // conv_generic_kernel_tiled  pixels on lanes with a run-time window, stride,
 //                      channel count, bit-widths and encodings
 //                      (conv_tiled.h); serves what the pixel kernel does not.
+// dense_rows_kernel    the reduction on the lanes (dense_rows.hip), for matrix
+//                      products of few rows.
 // conv_generic_kernel  one output per thread, runtime everything; serves
 //                      every remaining shape (a single image or a filter set
 //                      past 2 GiB) and kernel mode 1.
@@ -41,6 +43,7 @@
 #include "conv_fast.h"
 #include "conv_pix.h"
 #include "conv_tiled.h"
+#include "dense_rows.h"
 
 namespace bs {
 namespace {
@@ -646,14 +649,15 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
     return hipSuccess;
 }
 
-enum class Family { kPixels, kChannels, kTiled, kGeneric };
+enum class Family { kPixels, kChannels, kTiled, kRows, kGeneric };
 
-// The kernel family a call takes: mode 0 tries pixels-on-lanes, then the
-// tiled generic kernel, then the plain one; 3 and 2 try only their own family
+// The kernel family a call takes: mode 0 tries the kernel for products of few
+// rows, pixels-on-lanes, the tiled generic kernel, then the plain one; 3 and 2 try only their own family
 // (pixels- or channels-on-lanes) before the plain generic kernel; 1 is that
 // one only.
 Family choose(const ConvShape& s, int mode, pix::PixKernelFn* pfn,
               pix::PlanInfo* info) {
+    if (mode == 0 && rows::covers(s)) return Family::kRows;
     if (mode == 0 || mode == 3) {
         if ((*pfn = pix_kernel_for(s, false, pix::kSrcPacked, info)) !=
             nullptr)
@@ -686,6 +690,8 @@ hipError_t launch_conv(const ConvShape& s, const uint32_t* act,
                                           g.cw);
             return launch(fn, grid, dim3(kBlock), lds, st, act, wts, out, g);
         }
+        case Family::kRows:
+            return rows::launch_rows(s, act, wts, out, st);
         case Family::kTiled:
             return tiled::launch_conv(s, act, wts, out, nullptr, device_cus(),
                                       st);
@@ -883,6 +889,8 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
                             pick_group_pixels(s.ow), cw, grid.x, grid.y,
                             kBlock, lds);
         }
+        case Family::kRows:
+            return rows::describe(s, enc, buf, len);
         case Family::kTiled:
             return tiled::describe(s, enc, device_cus(), buf, len);
         case Family::kGeneric:

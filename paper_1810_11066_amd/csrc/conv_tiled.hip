@@ -16,18 +16,6 @@ TiledKernelFn pick(int a, int w, int cb, int c, bool xnor, bool req) {
     }
 }
 
-// Planes of a group when `bits` planes are split evenly into groups of at
-// most 4 (5 -> 3 + 2, 8 -> 4 + 4).
-int plane_groups(int bits) { return (bits + 3) / 4; }
-int group_planes(int bits) {
-    return (bits + plane_groups(bits) - 1) / plane_groups(bits);
-}
-
-void plane_weights(int bits, int enc, int32_t (&w)[8]) {
-    for (int i = 0; i < 8; ++i) w[i] = i < bits ? 1 << i : 0;
-    if (enc == kSigned) w[bits - 1] = -w[bits - 1];
-}
-
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct Plan {
@@ -67,8 +55,8 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     const int cw = (s.c + 31) / 32;
     pl.a = group_planes(s.abits);
     pl.w = group_planes(s.wbits);
-    pl.xnor = s.aenc == kBipolar && s.wenc == kBipolar && s.abits == 1 &&
-              s.wbits == 1;
+    const Encoding e = encoding_terms(s);
+    pl.xnor = e.xnor;
     // words per chunk: 3 or 4, whichever reads fewer past the plane (4 when
     // equal: fewer steps)
     pl.cb = cw < 4 ? cw : ceil_div(cw, 3) * 3 < ceil_div(cw, 4) * 4 ? 3 : 4;
@@ -91,13 +79,7 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     g.ch_step = ch_step;
     plane_weights(s.abits, s.aenc, g.pa);
     plane_weights(s.wbits, s.wenc, g.pw8);
-    const int aa = s.aenc == kBipolar ? 2 : 1, aw = s.wenc == kBipolar ? 2 : 1;
-    const int ba = s.aenc == kBipolar ? 1 - (1 << s.abits) : 0;
-    const int bw = s.wenc == kBipolar ? 1 - (1 << s.wbits) : 0;
-    g.cs = aa * aw; g.csa = aa * bw; g.csw = ba * aw; g.cn = ba * bw;
-    if (pl.xnor) {
-        g.cs = -2; g.csa = g.csw = 0; g.cn = 1;
-    }
+    g.cs = e.cs; g.csa = e.csa; g.csw = e.csw; g.cn = e.cn;
     g.out_scale = rq ? rq->scale : 0.0f;
     g.out_bits = rq ? rq->bits : 0;
     g.out_qmax = rq ? (float)((1 << rq->bits) - 1) : 0.0f;

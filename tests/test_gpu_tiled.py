@@ -3,7 +3,8 @@ shapes no specialisation covers, against the oracle: every group of planes
 (1-8 bits), chunk width (1-4 words, whole and partial last chunks), channel
 tile and remainder, window, stride and padding, the encodings' corrections,
 waves that share a unit's steps, operands swapped for products of few rows,
-and requantized output."""
+and requantized output; and of dense_rows_kernel, which serves products of few
+rows and many words."""
 import numpy as np
 import pytest
 import torch
@@ -114,12 +115,17 @@ def test_conv_tiles(oracle, npix, oc):
                  abits, wbits, U, U)
 
 
-@pytest.mark.parametrize("m", [1, 2, 5, 18, 47, 63, 64])
-@pytest.mark.parametrize("n,k", [(1, 40), (70, 100), (129, 800), (1000, 352)])
+@pytest.mark.parametrize("m", [1, 2, 5, 16, 18, 32, 47, 63, 64])
+@pytest.mark.parametrize("n,k", [(1, 40), (70, 100), (129, 800), (1000, 352),
+                                 (3, 768), (34, 2080), (6, 4150)])
 def test_dense_few_rows(oracle, m, n, k):
-    """Matrix products of few rows, both ways round, over the encodings."""
+    """Matrix products of few rows over the encodings: the reduction on the
+    lanes (from 24 words per plane, whole and partial chunks of 64 words, row
+    and channel tiles with remainders), and pixels or output channels on
+    them."""
     for abits, wbits, aenc, wenc in ((1, 1, U, U), (2, 2, U, S), (1, 3, B, U),
-                                     (2, 1, U, B), (1, 1, B, B)):
+                                     (2, 1, U, B), (1, 1, B, B), (4, 4, S, S),
+                                     (4, 2, B, B), (6, 5, S, B)):
         say("dense", m, n, k, abits, wbits, aenc, wenc)
         rng = np.random.default_rng(m * 1000 + n + k)
         a = rng.integers(0, 1 << abits, size=(m, k), dtype=np.uint8)
@@ -129,6 +135,11 @@ def test_dense_few_rows(oracle, m, n, k):
                                 wenc)
         want = oracle.conv2d(op, ap.reshape(1, 1, m, abits, -1),
                              wp.reshape(n, 1, 1, wbits, -1)).reshape(m, n)
+        rows = (m <= 16 and k > 23 * 32) or (m <= 32 and k > 95 * 32)
+        p = bs.ConvParams(1, 1, m, k, n, 1, 1, 1, 1, 0, 0, abits, wbits, aenc,
+                          wenc)
+        assert bs.bs_conv2d_describe(p).startswith(
+            "dense_rows_kernel") == rows
         g = Guarded(m * n)
         bs.bs_dense_ex(m, n, k, abits, aenc, wbits, wenc,
                        dev(ap.view(np.int32)), dev(wp.view(np.int32)), g.t)
