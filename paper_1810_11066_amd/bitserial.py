@@ -136,9 +136,12 @@ def _check(status: int):
 
 
 def _stream(stream=None):
+    """Handle of the given stream, or of the current device's current one.
+    (torch.cuda.current_stream() builds a Stream object around the same
+    handle: 2.5 us against 0.1 us, in calls that launch a 4 us kernel.)"""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _dev(t: torch.Tensor, name: str, dtype: torch.dtype, numel: int):
@@ -267,17 +270,33 @@ def bs_conv2d_quantized_describe(p: ConvParams) -> str:
     return buf.value.decode()
 
 
-def bs_conv2d(p: ConvParams, act_packed: torch.Tensor, w_packed: torch.Tensor,
-              out: torch.Tensor, stream=None) -> None:
-    lib = load_library()
-    oh, ow = _out_hw(p)
-    cw = words(p.c)
-    _check(lib.bs_conv2d(
-        ctypes.byref(p),
+def _conv2d(p: ConvParams, oh: int, ow: int, act_packed, w_packed, out,
+            stream=None) -> None:
+    cw = (p.c + 31) // 32
+    _check(load_library().bs_conv2d(
+        p,
         _dev(act_packed, "act_packed", torch.int32,
              p.n * p.h * p.w * p.abits * cw),
         _dev(w_packed, "w_packed", torch.int32,
              p.oc * p.kh * p.kw * p.wbits * cw),
+        _dev(out, "out", torch.int32, p.n * oh * ow * p.oc),
+        _stream(stream)))
+
+
+def bs_conv2d(p: ConvParams, act_packed: torch.Tensor, w_packed: torch.Tensor,
+              out: torch.Tensor, stream=None) -> None:
+    oh, ow = _out_hw(p)
+    _conv2d(p, oh, ow, act_packed, w_packed, out, stream)
+
+
+def _conv2d_codes(p: ConvParams, oh: int, ow: int, act_codes, w_packed, out,
+                  stream=None) -> None:
+    c = p.c
+    _check(load_library().bs_conv2d_codes(
+        p,
+        _dev(act_codes, "act_codes", torch.uint8, p.n * p.h * p.w * c),
+        _dev(w_packed, "w_packed", torch.int32,
+             p.oc * p.kh * p.kw * p.wbits * ((c + 31) // 32)),
         _dev(out, "out", torch.int32, p.n * oh * ow * p.oc),
         _stream(stream)))
 
@@ -287,13 +306,7 @@ def bs_conv2d_codes(p: ConvParams, act_codes: torch.Tensor,
                     stream=None) -> None:
     """bs_pack of the uint8 NHWC codes fused into bs_conv2d."""
     oh, ow = _out_hw(p)
-    _check(load_library().bs_conv2d_codes(
-        ctypes.byref(p),
-        _dev(act_codes, "act_codes", torch.uint8, p.n * p.h * p.w * p.c),
-        _dev(w_packed, "w_packed", torch.int32,
-             p.oc * p.kh * p.kw * p.wbits * words(p.c)),
-        _dev(out, "out", torch.int32, p.n * oh * ow * p.oc),
-        _stream(stream)))
+    _conv2d_codes(p, oh, ow, act_codes, w_packed, out, stream)
 
 
 def bs_conv2d_quantized(p: ConvParams, act: torch.Tensor, act_scale: float,
@@ -490,7 +503,7 @@ def conv2d(spec: Conv2dSpec, act_packed: torch.Tensor,
     oh, ow = _out_hw(p)
     out = torch.empty((spec.n, oh, ow, spec.oc), dtype=torch.int32,
                       device=act_packed.device)
-    bs_conv2d(p, act_packed, w_packed, out)
+    _conv2d(p, oh, ow, act_packed, w_packed, out)
     return out
 
 
@@ -501,7 +514,7 @@ def conv2d_codes(spec: Conv2dSpec, act_codes: torch.Tensor,
     oh, ow = _out_hw(p)
     out = torch.empty((spec.n, oh, ow, spec.oc), dtype=torch.int32,
                       device=act_codes.device)
-    bs_conv2d_codes(p, act_codes, w_packed, out)
+    _conv2d_codes(p, oh, ow, act_codes, w_packed, out)
     return out
 
 
