@@ -75,6 +75,25 @@ __device__ __forceinline__ uint32_t nibble_of(uint32_t v, int b) {
     return (x | (x >> 14)) & 0xFu;      // bits 0..3
 }
 
+// Bit-plane b of 32 codes held as bytes in d[0..7] (code 4 m + k in byte k of
+// d[m]): bit u of the result is bit b of code u.  Per dword the plane's bits
+// are masked (bit b of each byte) and one v_dot4_u32_u8 against the byte
+// weights 2^k (or 2^(4+k) for the second dword of a pair) adds them, shifted
+// by b, into one byte of 8 codes; four such bytes make the word.
+__device__ __forceinline__ uint32_t plane_word(const uint32_t (&d)[8], int b) {
+    const uint32_t m = 0x01010101u << b;
+    uint32_t byte[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        byte[j] = __builtin_amdgcn_udot4(d[2 * j] & m, 0x08040201u, 0u, false);
+        byte[j] = __builtin_amdgcn_udot4(d[2 * j + 1] & m, 0x80402010u,
+                                         byte[j], false);
+    }
+    // byte[j] holds codes 8 j .. 8 j + 7 at bits b .. b + 7
+    const uint32_t lo24 = byte[0] | byte[1] << 8 | byte[2] << 16;
+    return (lo24 >> b) | (byte[3] >> b) << 24;
+}
+
 // ---- kernel launch -------------------------------------------------------
 
 // The calling host thread's timing events (bs_set_timing_events); both

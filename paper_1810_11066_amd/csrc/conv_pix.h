@@ -578,30 +578,12 @@ struct Window {
 
 // ---- staged activations ---------------------------------------------------
 
-// Bit-planes 0..A-1 of 32 codes held as bytes in d[0..7] (code 4 m + k in
-// byte k of d[m]): bit u of plane word b is bit b of code u.  Per plane and
-// dword, the plane's bits are masked (bit b of each byte) and one
-// v_dot4_u32_u8 against the byte weights 2^k (or 2^(4+k) for the second
-// dword of a pair) adds them, shifted by b, into one byte of 8 codes; four
-// such bytes make the word.
+// Bit-planes 0..A-1 of 32 codes held as bytes in d[0..7] (plane_word).
 template <int A>
 __device__ __forceinline__ void pack32_planes(const uint32_t (&d)[8],
                                               uint32_t (&w)[A]) {
 #pragma unroll
-    for (int b = 0; b < A; ++b) {
-        const uint32_t m = 0x01010101u << b;
-        uint32_t byte[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            byte[j] = __builtin_amdgcn_udot4(d[2 * j] & m, 0x08040201u, 0u,
-                                             false);
-            byte[j] = __builtin_amdgcn_udot4(d[2 * j + 1] & m, 0x80402010u,
-                                             byte[j], false);
-        }
-        // byte[j] holds codes 8 j .. 8 j + 7 at bits b .. b + 7
-        const uint32_t lo24 = byte[0] | byte[1] << 8 | byte[2] << 16;
-        w[b] = (lo24 >> b) | (byte[3] >> b) << 24;
-    }
+    for (int b = 0; b < A; ++b) w[b] = plane_word(d, b);
 }
 
 // The 32 codes of one staged item (channels 32 t .. 32 t + 31 of one input
