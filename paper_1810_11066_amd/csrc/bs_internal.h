@@ -44,6 +44,18 @@ __device__ __forceinline__ uint32_t quant_code(float x, float scale,
     return (uint32_t)r;
 }
 
+// Unipolar code of x inserted as byte k of `bytes`: v_med3_f32 clamps the
+// product to [0, qmax] (a NaN gives the smallest of the others, 0), and
+// v_cvt_pk_u8_f32 rounds half to even and inserts the byte.  The bounds are
+// whole numbers, so clamping first rounds to the same code as quant_code, in
+// 3 instructions for the 6 of rounding, two clamps, conversion and shift-or.
+__device__ __forceinline__ uint32_t quant_insert(float x, float scale,
+                                                 float qmax, uint32_t k,
+                                                 uint32_t bytes) {
+    return __builtin_amdgcn_cvt_pk_u8_f32(
+        __builtin_amdgcn_fmed3f(x * scale, 0.0f, qmax), k, bytes);
+}
+
 // Signed (two's complement) code: round-half-to-even of the binary32
 // product clamped to [-(hmax + 1), hmax] with NaN sent to 0, returned as its
 // low bits (hmax = 2^(bits-1) - 1).
@@ -92,6 +104,15 @@ __device__ __forceinline__ uint32_t plane_word(const uint32_t (&d)[8], int b) {
     // byte[j] holds codes 8 j .. 8 j + 7 at bits b .. b + 7
     const uint32_t lo24 = byte[0] | byte[1] << 8 | byte[2] << 16;
     return (lo24 >> b) | (byte[3] >> b) << 24;
+}
+
+// Bit b of 8 codes held as bytes (codes 0..3 in lo, 4..7 in hi) as one byte.
+__device__ __forceinline__ uint32_t plane_byte(uint32_t lo, uint32_t hi,
+                                               int b) {
+    const uint32_t m = 0x01010101u << b;
+    uint32_t x = __builtin_amdgcn_udot4(lo & m, 0x08040201u, 0u, false);
+    x = __builtin_amdgcn_udot4(hi & m, 0x80402010u, x, false);
+    return x >> b;
 }
 
 // ---- kernel launch -------------------------------------------------------

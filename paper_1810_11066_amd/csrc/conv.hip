@@ -429,6 +429,13 @@ void plan_pix_lds(const ConvShape& s, pix::PixKernelFn fn, int forced_run,
     int64_t best = lmin;
     for (int64_t l = lmin + 1; l <= 2 * lmin; ++l)
         if (load(l) < load(best)) best = l;
+    // requantized output leaves by single bytes whatever the run, so shorter
+    // runs in more than one round may also balance the CUs (ResNet-18 layers
+    // 9 and 12 at batch 128: 12544 units in runs of 2 give some CUs 7 blocks
+    // and most 6; in runs of 1, 13 and 12)
+    if (rq)
+        for (int64_t l = lmin - 1; 2 * l >= lmin && l >= 1; --l)
+            if (load(l) < load(best)) best = l;
     // 1x1 layers with few word pairs per result (A W words <= 16) are bound
     // by their int32 stores, not by the vector ALUs: runs of one tile chunk
     // of quads make every flush write whole 64-byte pieces of the pixel

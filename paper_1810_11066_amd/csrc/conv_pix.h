@@ -273,9 +273,7 @@ struct PackedOut {
     uint32_t codes[2];   // the codes of each quad, one byte per channel
 
     __device__ __forceinline__ void clear() { codes[0] = codes[1] = 0; }
-    // codes of the 4 channels of quad `half` (0 or 1) of the byte: the int32
-    // results are exact in float32 (far below 2^24) and never NaN, so the
-    // clamp of the quantizer is one v_med3
+    // codes of the 4 channels of quad `half` (0 or 1) of the byte
     __device__ __forceinline__ void add4(const uint32_t (&val)[4],
                                          const PixArgs& g, int half) {
         add4(val, g.out_scale, g, half);
@@ -285,12 +283,9 @@ struct PackedOut {
                                          int half) {
         uint32_t bytes = 0;
 #pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            const float r =
-                __builtin_rintf((float)(int32_t)val[o] * scale);
-            bytes |= (uint32_t)__builtin_amdgcn_fmed3f(r, 0.0f, g.out_qmax)
-                     << (8 * o);
-        }
+        for (int o = 0; o < 4; ++o)
+            bytes = quant_insert((float)(int32_t)val[o], scale, g.out_qmax,
+                                 (uint32_t)o, bytes);
         // (selects, not an indexed store: a runtime index into a register
         // array would go through scratch memory)
         codes[0] = half ? codes[0] : bytes;
@@ -310,8 +305,7 @@ struct PackedOut {
         for (int b = 0; b < 8; ++b)
             if (b < g.out_bits) {
                 uint8_t* d = dst + (size_t)b * (uint32_t)(4 * g.out_words);
-                d[0] = (uint8_t)(nibble_of(codes[0], b) |
-                                 nibble_of(codes[1], b) << 4);
+                d[0] = (uint8_t)plane_byte(codes[0], codes[1], b);
                 for (int z = 1; z <= pad; ++z) d[z] = 0;
             }
     }
@@ -589,7 +583,7 @@ __device__ __forceinline__ void pack32_planes(const uint32_t (&d)[8],
 // The 32 codes of one staged item (channels 32 t .. 32 t + 31 of one input
 // pixel, starting at element e of the NHWC activations) as bytes in d[0..7]
 // (code 4 m + k in byte k of d[m]).  Codes: two 16-byte loads.  Float32:
-// eight, each value quantized as bs_quantize does (quant_code).  in false
+// eight, each value quantized as bs_quantize does (quant_insert).  in false
 // (a pixel in the padding): the loads fall past the buffer and read zeros,
 // which are code 0 either way.
 template <int SRC>
@@ -603,10 +597,11 @@ __device__ __forceinline__ void load_item(uint32_t (&d)[8], Rsrc src,
             const float4 f = __builtin_bit_cast(
                 float4, __builtin_amdgcn_raw_buffer_load_b128(
                             src, off + 16u * (uint32_t)m, 0, 0));
-            d[m] = quant_code<false>(f.x, g.in_scale, g.in_qmax) |
-                   quant_code<false>(f.y, g.in_scale, g.in_qmax) << 8 |
-                   quant_code<false>(f.z, g.in_scale, g.in_qmax) << 16 |
-                   quant_code<false>(f.w, g.in_scale, g.in_qmax) << 24;
+            uint32_t c4 = 0;
+            c4 = quant_insert(f.x, g.in_scale, g.in_qmax, 0, c4);
+            c4 = quant_insert(f.y, g.in_scale, g.in_qmax, 1, c4);
+            c4 = quant_insert(f.z, g.in_scale, g.in_qmax, 2, c4);
+            d[m] = quant_insert(f.w, g.in_scale, g.in_qmax, 3, c4);
         }
     } else {
         const uint32_t off = in ? e : kOutOfRange;

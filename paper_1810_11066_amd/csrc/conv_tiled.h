@@ -468,11 +468,14 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
             uint32_t v[8];
             values(v, lane, b8 * 8);
 #pragma unroll
-            for (int o = 0; o < 8; ++o) {
-                const uint32_t code = quant_code<false>(
-                    (float)(int32_t)v[o], g.out_scale, g.out_qmax);
-                if (8 * k8 + o < g.oc) codes[o >> 2] |= code << (8 * (o & 3));
-            }
+            for (int o = 0; o < 8; ++o)
+                codes[o >> 2] = quant_insert(
+                    (float)(int32_t)v[o], g.out_scale, g.out_qmax,
+                    (uint32_t)(o & 3), codes[o >> 2]);
+            // channels past the last one have code 0
+            const int n = g.oc - 8 * k8;
+            if (n < 8) codes[1] &= n > 4 ? ~0u >> 8 * (8 - n) : 0u;
+            if (n < 4) codes[0] &= ~0u >> 8 * (4 - n);
             if (p >= g.npix) continue;
             uint8_t* dst = reinterpret_cast<uint8_t*>(out) +
                            (size_t)p * (uint32_t)(4 * g.out_bits *
@@ -482,8 +485,7 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
             const int pad = k8 == last ? 3 - (k8 & 3) : 0;
             for (int b = 0; b < g.out_bits; ++b) {
                 uint8_t* d = dst + (size_t)b * (uint32_t)(4 * g.out_words);
-                d[0] = (uint8_t)(nibble_of(codes[0], b) |
-                                 nibble_of(codes[1], b) << 4);
+                d[0] = (uint8_t)plane_byte(codes[0], codes[1], b);
                 for (int z = 1; z <= pad; ++z) d[z] = 0;
             }
         }

@@ -49,6 +49,12 @@ __device__ __forceinline__ uint32_t code_of(float x, float scale, float qmax) {
 
 template <int ENC>
 __device__ __forceinline__ uint32_t codes4(float4 f, float scale, float qmax) {
+    if constexpr (ENC == kUnipolar) {
+        uint32_t c4 = quant_insert(f.x, scale, qmax, 0, 0u);
+        c4 = quant_insert(f.y, scale, qmax, 1, c4);
+        c4 = quant_insert(f.z, scale, qmax, 2, c4);
+        return quant_insert(f.w, scale, qmax, 3, c4);
+    }
     return code_of<ENC>(f.x, scale, qmax) |
            (code_of<ENC>(f.y, scale, qmax) << 8) |
            (code_of<ENC>(f.z, scale, qmax) << 16) |

@@ -99,6 +99,29 @@ def test_pack_strided(oracle, shape, layout, bits):
     assert np.array_equal(g.words().reshape(want.shape), want)
 
 
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_quantize_halves(oracle, bits):
+    """Every value half way between two codes, its float32 neighbours, the
+    ends of the range and the special values, through each unipolar
+    quantizer: round half to even, then clamp."""
+    h = np.arange(-4, 2 * (1 << bits) + 4, dtype=np.float32) / 2
+    x = np.concatenate([h, np.nextafter(h, np.float32(np.inf)),
+                        np.nextafter(h, np.float32(-np.inf)),
+                        np.array([np.nan, np.inf, -np.inf, -0.0, 1e-42, -1e-42,
+                                  3e38, -3e38], dtype=np.float32)])
+    x = np.resize(x, (x.size + 63) // 64 * 64).astype(np.float32)
+    say("halves", bits, x.size)
+    want = oracle.quantize(x, 1.0, bits)
+    q = torch.empty(x.size, dtype=torch.uint8, device="cuda")
+    bs.bs_quantize(dev(x), q, 1.0, bits)
+    assert np.array_equal(q.cpu().numpy(), want)
+    for k in (64, 8):
+        g = Guarded(x.size // k * bits * ((k + 31) // 32))
+        bs.bs_quantize_pack(dev(x), g.t, x.size // k, k, 1.0, bits)
+        wp = oracle.pack(want.reshape(-1, k), bits)
+        assert np.array_equal(g.words().reshape(wp.shape), wp)
+
+
 def test_more_than_2_31_chunks():
     """Row numbers past 32 bits: 2^31 + 100 rows of one code (each row one
     chunk) pack to their own low bit."""
