@@ -22,8 +22,8 @@
 //
 // Measured against what served these shapes before (one output per thread):
 // 32 x 27 x 27 x 96 -> 150 channels, 3x3, A2 x bipolar W1, quantize+pack
-// included: 290 -> 29.3 us a pass; 100 x 784 x 1000 product, A2W2: 65.8 ->
-// 18.8 us.
+// included: 290 -> 27.5 us a pass; 100 x 784 x 1000 product, A2W2: 64.6 ->
+// 13.6 us (of which the host takes most).
 //
 // Filter words come through s_buffer_load, whose range check makes the last
 // channel tile and the over-read of a 3-word chunk safe without clamping.
@@ -74,7 +74,7 @@ struct TiledArgs {
     int32_t pix_step, ch_step;       // int32 output strides, in elements
     int32_t pa[8], pw8[8];           // plane weights, 0 past the last plane
     int32_t cs, csa, csw, cn;
-    FastDiv div_ow, div_oh, div_cols;
+    FastDiv div_ow, div_oh, div_cols, div_nch, div_kw;
     // requantized output
     float out_scale, out_qmax;
     int32_t out_bits, out_words;
@@ -217,14 +217,14 @@ __device__ __forceinline__ void load_words(uint32_t (&p)[A][CB], Rsrc act,
 // and W filter planes (byte offsets wp within a tap) for the C channels from
 // filter byte offset ch0: adds to the lane's tile row (or, with `first`, sets
 // it to)
-//   sum_ij scale pa[i] pw[j] popcount(a_i AND w_j)
-// and adds the pa-weighted activation popcounts to sa.
+//   add + sum_ij scale pa[i] pw[j] popcount(a_i AND w_j)
+//       + csa sum_i pa[i] popcount(a_i).
 template <int A, int W, int CB, int C, bool XN, bool ONES>
 __device__ __forceinline__ void reduce(
-    uint32_t* trow, bool first, uint32_t& sa, const TiledArgs& g,
+    uint32_t* trow, bool first, uint32_t add, const TiledArgs& g,
     const Window& win, Rsrc act, v4i rw, int t0, int t1,
     const uint32_t (&ap)[A], const uint32_t (&wp)[W], uint32_t ch0,
-    const int (&pa)[A], const int (&pw)[W], int scale, bool want_sa) {
+    const int (&pa)[A], const int (&pw)[W], int scale, int csa) {
     constexpr int SC = slice_channels<W, CB, C>();
     constexpr int NSL = C / SC;
     static_assert(NSL % 2 == 0, "slice buffers alternate within a step");
@@ -239,9 +239,10 @@ __device__ __forceinline__ void reduce(
 #pragma unroll
             for (int j = 0; j < W; ++j) acc[o][i][j] = 0;
 
+    uint32_t sa = 0;
     Step st;
-    const int tap = t0 / g.nch;
-    st.r = tap / g.kw;
+    const int tap = (int)g.div_nch.div((uint32_t)t0);
+    st.r = (int)g.div_kw.div((uint32_t)tap);
     st.s = tap - st.r * g.kw;
     st.c0 = (t0 - tap * g.nch) * CB;
     st.cs = min(st.c0, g.cw - CB);
@@ -274,7 +275,7 @@ __device__ __forceinline__ void reduce(
                 for (int i = 0; i < A; ++i) p[i][k] &= m;
             }
         }
-        if (want_sa) {
+        if (csa != 0) {
 #pragma unroll
             for (int i = 0; i < A; ++i) {
                 uint32_t n = 0;
@@ -324,9 +325,11 @@ __device__ __forceinline__ void reduce(
 #pragma unroll
             for (int k = 0; k < CB; ++k) p[i][k] = pn[i][k];
     }
+    if (csa != 0) add += (uint32_t)csa * sa;
 #pragma unroll
     for (int o = 0; o < C; ++o) {
-        uint32_t v = first ? 0u : trow[o];
+        uint32_t v = add;
+        if (!first) v += trow[o];
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
@@ -373,13 +376,14 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
         win.base = ((img * (uint32_t)g.h + (uint32_t)win.iy0) *
                         (uint32_t)g.w + (uint32_t)win.ix0) *
                    (4u * (uint32_t)(g.abits * g.cw));
-        // in-range channel values of the window
-        const int nr = max(min(win.iy0 + g.kh, g.h) - max(win.iy0, 0), 0);
-        const int nc = max(min(win.ix0 + g.kw, g.w) - max(win.ix0, 0), 0);
-        const uint32_t konst =
-            ks == 0 ? (uint32_t)g.cn * (uint32_t)(nr * nc) * (uint32_t)g.c
-                    : 0u;
-        // this wave's steps
+        // the term of the window's in-range channel values
+        uint32_t konst = 0;
+        if (g.cn != 0 && ks == 0) {
+            const int nr = max(min(win.iy0 + g.kh, g.h) - max(win.iy0, 0), 0);
+            const int nc = max(min(win.ix0 + g.kw, g.w) - max(win.ix0, 0), 0);
+            konst = (uint32_t)g.cn * (uint32_t)(nr * nc) * (uint32_t)g.c;
+        }
+        // this wave's steps (at least one: the host shares them out so)
         const int t0 = (int)((int64_t)g.nsteps * ks >> g.ks_log2);
         const int t1 = (int)((int64_t)g.nsteps * (ks + 1) >> g.ks_log2);
         const uint32_t ch_bytes =
@@ -387,53 +391,42 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
 #pragma unroll 1
         for (int sub = 0; sub < g.nsub; ++sub) {
             uint32_t* trow = tile + lane * kStride + sub * C;
-            uint32_t sa = 0;
             bool first = true;
             const uint32_t ch0 = (uint32_t)(col0 + sub * C) * ch_bytes;
-            if (t0 < t1) {
 #pragma unroll 1
-                for (int wg = 0; wg < g.wt_groups; ++wg) {
-                    uint32_t wp[W];
-                    int pw[W];
+            for (int wg = 0; wg < g.wt_groups; ++wg) {
+                uint32_t wp[W];
+                int pw[W];
 #pragma unroll
-                    for (int j = 0; j < W; ++j) {
-                        pw[j] = g.pw8[wg * W + j];
-                        wp[j] = 4u * (uint32_t)(
-                                    min(wg * W + j, g.wbits - 1) * g.cw);
-                    }
+                for (int j = 0; j < W; ++j) {
+                    pw[j] = g.pw8[wg * W + j];
+                    wp[j] =
+                        4u * (uint32_t)(min(wg * W + j, g.wbits - 1) * g.cw);
+                }
 #pragma unroll 1
-                    for (int ag = 0; ag < g.act_groups; ++ag) {
-                        uint32_t ap[A];
-                        int pa[A];
+                for (int ag = 0; ag < g.act_groups; ++ag) {
+                    uint32_t ap[A];
+                    int pa[A];
 #pragma unroll
-                        for (int i = 0; i < A; ++i) {
-                            pa[i] = g.pa[ag * A + i];
-                            ap[i] = 4u * (uint32_t)(
-                                        min(ag * A + i, g.abits - 1) * g.cw);
-                        }
-                        reduce<A, W, CB, C, XN, false>(
-                            trow, first, sa, g, win, ract, rw, t0, t1, ap, wp,
-                            ch0, pa, pw, g.cs, g.csa != 0 && wg == 0);
-                        first = false;
+                    for (int i = 0; i < A; ++i) {
+                        pa[i] = g.pa[ag * A + i];
+                        ap[i] = 4u * (uint32_t)(
+                                    min(ag * A + i, g.abits - 1) * g.cw);
                     }
-                    if constexpr (!XN) {
-                        if (g.csw != 0) {
-                            const uint32_t none[1] = {0};
-                            const int one[1] = {1};
-                            reduce<1, W, CB, C, false, true>(
-                                trow, false, sa, g, win, ract, rw, t0, t1,
-                                none, wp, ch0, one, pw, g.csw, false);
-                        }
+                    reduce<A, W, CB, C, XN, false>(
+                        trow, first, first ? konst : 0u, g, win, ract, rw, t0,
+                        t1, ap, wp, ch0, pa, pw, g.cs, wg == 0 ? g.csa : 0);
+                    first = false;
+                }
+                if constexpr (!XN) {
+                    if (g.csw != 0) {
+                        const uint32_t none[1] = {0};
+                        const int one[1] = {1};
+                        reduce<1, W, CB, C, false, true>(
+                            trow, false, 0u, g, win, ract, rw, t0, t1, none,
+                            wp, ch0, one, pw, g.csw, 0);
                     }
                 }
-            }
-            // terms of the lane alone, and the tile row of a wave without
-            // steps
-            const uint32_t add = konst + (uint32_t)g.csa * sa;
-            if (first || g.csa != 0 || g.cn != 0) {
-#pragma unroll
-                for (int o = 0; o < C; ++o)
-                    trow[o] = (first ? 0u : trow[o]) + add;
             }
         }
     }
@@ -504,7 +497,8 @@ void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
                 __builtin_amdgcn_raw_buffer_store_b32(
                     v[0], rout, in ? off : kOutOfRange, 0, 0);
             }
-        } else if (g.oc % 4 == 0) {
+        } else if (g.oc % 4 == 0 || col0 + cols <= g.oc) {
+            // whole quads of channels (dword-aligned 16-byte stores)
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
             const int nq = cols >> 2;            // quads per pixel: 1, 2, 4
             const int lg = nq == 4 ? 2 : nq == 2 ? 1 : 0;

@@ -86,12 +86,15 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     g.out_words = (s.oc + 31) / 32;
     g.div_ow.init((uint32_t)s.ow);
     g.div_oh.init((uint32_t)s.oh);
+    g.div_nch.init((uint32_t)g.nch);
+    g.div_kw.init((uint32_t)s.kw);
 
     // The tile: the widest one, unless a quarter of its channels would be
     // padding; narrower units, then waves sharing a unit's steps, then
-    // 4-channel tiles, until there are 4 waves for every SIMD.
+    // 4-channel tiles, until there are 3 waves for every SIMD (each narrowing
+    // repeats a wave's set-up, about 250 vector instructions).
     const int64_t groups = ceil_div(g.npix, 64);
-    const int64_t want = (int64_t)cus * 4 * 4;
+    const int64_t want = (int64_t)cus * 4 * 3;
     const int least = rq ? 8 : 4;      // a packed byte is 8 channels
     pl.c = max_channels(pl.a, pl.w);
     if (4 * (int64_t)s.oc < 3 * ceil_div(s.oc, pl.c) * pl.c) pl.c = 4;
