@@ -311,11 +311,13 @@ __device__ __forceinline__ void reduce(
                     for (int i = 0; i < A; ++i)
 #pragma unroll
                         for (int o = 0; o < SC; ++o) {
-                            const uint32_t x =
-                                XN ? pix::xor_keep(p[i][k], keep[k],
-                                                   fs.w[o][j][k])
-                                   : p[i][k] & fs.w[o][j][k];
-                            pix::bcnt_acc(acc[sl * SC + o][i][j], x);
+                            uint32_t& n = acc[sl * SC + o][i][j];
+                            if constexpr (XN)
+                                pix::bcnt_acc(n, pix::xor_keep(
+                                                     p[i][k], keep[k],
+                                                     fs.w[o][j][k]));
+                            else
+                                pix::and_bcnt_acc(n, p[i][k], fs.w[o][j][k]);
                         }
             __builtin_amdgcn_sched_barrier(0);
         }
