@@ -449,6 +449,8 @@ void plan_pix_lds(const ConvShape& s, pix::PixKernelFn fn, int forced_run,
     if (forced_run > 0) best = forced_run;
     if (best > units) best = units;
     g->per_wave = (int32_t)best;
+    g->agent = best >= 2;
+    g->agent = best >= 2;
     const int64_t waves = (units + best - 1) / best;
     *grid = dim3((uint32_t)((waves + wpb - 1) / wpb));
 }
@@ -658,6 +660,38 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
 
 enum class Family { kPixels, kChannels, kTiled, kRows, kGeneric };
 
+// Shapes the tiled kernel serves faster than a pixel kernel that walks a long
+// reduction in blocks (nb > 1).  Units are 64 pixels x 4 channels.
+//
+// Few units, at most 3 per CU, so that most SIMDs have none or one wave: the
+// tiled kernel's waves share a unit's reduction.  Per launch, pixel kernel /
+// tiled: 7x7x512 -> 512 3x3 at batch 1 (128 units) A2W1 11.2 / 6.5, A3W3 34.7 /
+// 13.4 us, at batch 4 (512 units) 11.8 / 7.4 and 35.1 / 15.1, at batch 16 (1664
+// units) 16.2 / 17.9 and 38.6 / 39.5.  Products with 512 columns, k = 4096: 256
+// rows (512 units) A2W2 16.6 / 11.9, A4W4 54.8 / 24.0 us; 512 rows (1024
+// units) 16.9 / 19.2 and 55.4 / 41.4.  Problems of fewer than 16 units, which
+// were not measured, stay with the pixel kernel.
+//
+// One unit per wave in a full round (12 to 28 units per CU) with multi-bit
+// activations and 1-bit filters: a wave then loads A words per popcount chain
+// for 4 channels only, and the loads (9 TB/s from the L2s) take longer than
+// the arithmetic, while a tiled wave's 16 channels share them.  7x7x512 -> 512
+// at batch 64 (6272 units) 50.8 / 37.0 us, 9x9x512 -> 128 at batch 128 (5184)
+// 45.3 / 28.2, 256 x 4096 x 4096 (4096) 32.4 / 22.8; 9x9x512 -> 128 at batch
+// 64 (2592) 23.9 / 27.9.  A1W1 18.3 / 24.3 and A2W2 58.6 / 68.7 us on the first
+// of these shapes stay with the pixel kernel.
+bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
+    if (info.nb < 2) return false;
+    const int64_t units =
+        ((int64_t)s.n * s.oh * s.ow + 63) / 64 * (s.oc / 4);
+    const int64_t cus = device_cus();
+    if (!((units >= 16 && units <= 3 * cus) ||
+          (s.wbits == 1 && s.abits >= 2 && units >= 12 * cus &&
+           units <= pix::kWavesPerSimd * 4 * cus)))
+        return false;
+    return tiled::covers(s, false);
+}
+
 // The kernel family a call takes: mode 0 tries the kernel for products of few
 // rows, pixels-on-lanes, the tiled generic kernel, then the plain one; 3 and 2 try only their own family
 // (pixels- or channels-on-lanes) before the plain generic kernel; 1 is that
@@ -666,13 +700,13 @@ Family choose(const ConvShape& s, int mode, pix::PixKernelFn* pfn,
               pix::PlanInfo* info) {
     if (mode == 0 && rows::covers(s)) return Family::kRows;
     if (mode == 0 || mode == 3) {
-        if ((*pfn = pix_kernel_for(s, false, pix::kSrcPacked, info)) !=
-            nullptr)
+        *pfn = pix_kernel_for(s, false, pix::kSrcPacked, info);
+        if (*pfn && !(mode == 0 && tiled_is_faster(s, *info)))
             return Family::kPixels;
     }
     if (mode == 2 && conv_has_fast_path(s)) return Family::kChannels;
     if (mode == 0 && tiled::covers(s, false)) return Family::kTiled;
-    return Family::kGeneric;
+    return *pfn ? Family::kPixels : Family::kGeneric;
 }
 
 }  // namespace

@@ -108,6 +108,7 @@ struct PixArgs {
                            // words, the uint8 codes (kSrcCodes) or the
                            // float32 values (kSrcFloat)
     int32_t out_bytes;     // size of the int32 output, bytes (0: packed out)
+    int32_t agent;         // agent-scope stores allowed (out_store_policy)
     // activations staged in LDS (SRC != kSrcPacked): the most input pixels
     // any block's region holds (its LDS size)
     int32_t region_pixels;
@@ -373,7 +374,10 @@ __device__ __forceinline__ Rsrc make_rsrc(const void* p, int32_t bytes) {
 // 1-2.7 us shorter: less is left dirty for the write-back that ends each
 // launch.  For the 64-channel layers (2 words per plane) and the one-bit
 // activation kernels they are neutral or up to 4.7 us longer, and there the
-// default stays.
+// default stays.  So it does for runs of one unit (PixArgs::agent), whose
+// 16-byte pieces of the pixel rows would each go to memory by themselves (256
+// x 4096 x 4096 A2W2 37.1 us with agent scope, 36.2 us with the default; 14x14x256
+// -> 512 3x3 stride 2 at batch 64, A2W1, 32.2 and 30.6 us).
 constexpr int kStoreAgent = 16;
 template <int A, int CW>
 constexpr int out_store_policy() {
@@ -407,9 +411,9 @@ struct FlushMap {
 // data in registers at a time, for flushes that run while a large input
 // patch is held.  CPOL: the stores' cache policy (out_store_policy).
 template <bool SERIAL, int CPOL>
-__device__ __forceinline__ void flush_tile(const uint32_t* __restrict__ tile,
-                                           Rsrc out, const FlushMap& fm,
-                                           int oc_base, int nch, int lane) {
+__device__ __forceinline__ void flush_rounds(const uint32_t* __restrict__ tile,
+                                             Rsrc out, const FlushMap& fm,
+                                             int oc_base, int nch, int lane) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const uint32_t rstep = 4u * kFlushPixels * (uint32_t)fm.oc;  // per round
     const int q = lane % kFlushRounds, pr = lane / kFlushRounds;
@@ -426,6 +430,22 @@ __device__ __forceinline__ void flush_tile(const uint32_t* __restrict__ tile,
             v, out, in ? o0 + (uint32_t)r * rstep : kOutOfRange, 0, CPOL);
         if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// CPOL at run time: kernels with the agent-scope policy use it unless the
+// call's runs are single quads (agent false).
+template <bool SERIAL, int CPOL>
+__device__ __forceinline__ void flush_tile(const uint32_t* __restrict__ tile,
+                                           Rsrc out, const FlushMap& fm,
+                                           int oc_base, int nch, int lane,
+                                           bool agent) {
+    if constexpr (CPOL != 0) {
+        if (!agent) {
+            flush_rounds<SERIAL, 0>(tile, out, fm, oc_base, nch, lane);
+            return;
+        }
+    }
+    flush_rounds<SERIAL, CPOL>(tile, out, fm, oc_base, nch, lane);
 }
 
 // One output channel of the paired 1x1 conv: Eq. 2 over the centre tap's
@@ -1155,10 +1175,11 @@ void conv_pix_kernel(
             // entered, as it is re-entered, with the patch load followed by
             // one flush's stores, so the wait for the patch can leave those
             // in flight
-            flush_tile<kSerialFlush, kCpol>(tile, rout, v.fm, 0, 0, lane);
+            flush_tile<kSerialFlush, kCpol>(tile, rout, v.fm, 0, 0, lane,
+                                            g.agent);
             if constexpr (DUAL)
                 flush_tile<kSerialFlush, kCpol>(tile, rout1, v.fm, 0, 0,
-                                                lane);
+                                                lane, g.agent);
         }
         while (true) {
             if constexpr (kAhead) {
@@ -1227,7 +1248,8 @@ void conv_pix_kernel(
             auto flush_chunk = [&]() __attribute__((always_inline)) {
                 wave_lds_sync();
                 flush_tile<kSerialFlush, kCpol>(tile, rout, v.fm,
-                                                chunk_base, held * 4, lane);
+                                                chunk_base, held * 4, lane,
+                                                g.agent);
                 if constexpr (DUAL) {
                     wave_lds_sync();
                     uint32_t* row = tile + lane * kTileStride;
@@ -1241,7 +1263,7 @@ void conv_pix_kernel(
                     wave_lds_sync();
                     flush_tile<kSerialFlush, kCpol>(tile, rout1, v.fm,
                                                     chunk_base, held * 4,
-                                                    lane);
+                                                    lane, g.agent);
                 }
                 wave_lds_sync();
                 chunk_base += held * 4;
@@ -1402,7 +1424,7 @@ void conv_pix_kernel(
                 } else {
                     wave_lds_sync();
                     flush_tile<false, kCpol>(tile, rout, v.fm, 4 * sub,
-                                             nq * 4, lane);
+                                             nq * 4, lane, g.agent);
                     wave_lds_sync();
                 }
             }
@@ -1418,6 +1440,7 @@ using PixKernelFn = void (*)(const uint32_t*, const uint32_t*,
 struct PlanInfo {
     int ocb, ts, tb, cb;
     int enc;    // E of the specialisation: 3 * activation + weight encoding
+    int nb;     // reduction blocks
 };
 
 // Kernel for a supported (A, W, encodings, K, S, CW, requantized output) or
@@ -1474,6 +1497,7 @@ PixKernelFn pick_kscw(bool req, int src, bool dual, PlanInfo* info) {
         info->tb = Pl::TB;
         info->cb = Pl::CB;
         info->enc = E;
+        info->nb = Pl::NB;
         if (dual) {
             if constexpr (Pl::NB == 1 && K == 3 && W * CW <= 4 &&
                           (E == UU || E == UB)) {

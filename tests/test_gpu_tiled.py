@@ -146,6 +146,32 @@ def test_dense_few_rows(oracle, m, n, k):
         assert np.array_equal(g.numpy().reshape(m, n), want)
 
 
+@pytest.mark.parametrize("shape,abits,wbits,tiled", [
+    # n, h, w, c, oc, k, s: long reductions with few units of 64 pixels x 4
+    # channels (at most 768), and above
+    ((1, 7, 7, 512, 64, 3, 1), 2, 1, True),
+    ((2, 9, 9, 512, 1020, 3, 1), 3, 3, True),
+    ((2, 9, 9, 512, 1028, 3, 1), 3, 3, False),
+    ((1, 1, 200, 4096, 64, 1, 1), 2, 2, True),
+    # one unit per wave in a full round (3072 to 7168 units), A >= 2, W = 1
+    ((4, 14, 14, 256, 944, 3, 1), 2, 1, False),
+    ((4, 14, 14, 256, 948, 3, 1), 2, 1, True),
+    ((4, 14, 14, 256, 948, 3, 1), 1, 1, False),
+    ((1, 1, 64 * 28, 1024, 1024, 1, 1), 2, 1, True),
+    ((1, 1, 64 * 28 + 1, 1024, 1024, 1, 1), 2, 1, False)])
+def test_rule_for_long_reductions(oracle, shape, abits, wbits, tiled):
+    """The kernel on each side of the lines, and its results."""
+    n, h, w, c, oc, k, s = shape
+    say("long reduction", shape, abits, wbits)
+    ap, wp, want, p = operands(oracle, c + oc, n, h, w, c, oc, k, k, (s, s),
+                               (k // 2, k // 2), abits, wbits, U, U)
+    assert bs.bs_conv2d_describe(p).startswith(
+        "conv_generic_kernel_tiled" if tiled else "conv_pix_kernel")
+    g = Guarded(want.size)
+    bs.bs_conv2d(p, dev(ap.view(np.int32)), dev(wp.view(np.int32)), g.t)
+    assert np.array_equal(g.numpy().reshape(want.shape), want)
+
+
 @pytest.mark.parametrize("oc", [3, 8, 21, 40, 150])
 @pytest.mark.parametrize("obits", [1, 3, 8])
 def test_requant(oracle, oc, obits):
