@@ -450,7 +450,6 @@ void plan_pix_lds(const ConvShape& s, pix::PixKernelFn fn, int forced_run,
     if (best > units) best = units;
     g->per_wave = (int32_t)best;
     g->agent = best >= 2;
-    g->agent = best >= 2;
     const int64_t waves = (units + best - 1) / best;
     *grid = dim3((uint32_t)((waves + wpb - 1) / wpb));
 }
@@ -693,9 +692,9 @@ bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
 }
 
 // The kernel family a call takes: mode 0 tries the kernel for products of few
-// rows, pixels-on-lanes, the tiled generic kernel, then the plain one; 3 and 2 try only their own family
-// (pixels- or channels-on-lanes) before the plain generic kernel; 1 is that
-// one only.
+// rows, pixels-on-lanes, the tiled generic kernel, then the plain one; 3 and 2
+// try only their own family (pixels- or channels-on-lanes) before the plain
+// generic kernel; 1 is that one only.
 Family choose(const ConvShape& s, int mode, pix::PixKernelFn* pfn,
               pix::PlanInfo* info) {
     if (mode == 0 && rows::covers(s)) return Family::kRows;
