@@ -35,8 +35,15 @@
 // SA, SW the weighted popcounts of the in-range activation and filter words
 // and N the in-range channel values (conv_pix.h has the derivation).  SW is S
 // of an activation plane of ones on the in-range taps, computed by a pass of
-// the same loop.  +-1 data on both sides is N - 2 D, D counting
-// (a XOR w) AND in-range.
+// the same loop.  +-1 activations need no such pass: with
+// D_j = popcount((a XOR w_j) AND in-range), D_j = SA + SW_j - 2 S_j, so
+//   2 S_j - SW_j = SA - D_j
+// and one pass over D_j (the XOR and the mask are one instruction) replaces
+// those over S and SW, each as long.  (+-1 filters too: N - 2 D.)
+// Measured, packing included, with the pass over SW and without (A1, +-1):
+// 32 x 27 x 27 x 96 -> 150, 3x3, W2 43.0 -> 27.9 us; 64 x 28 x 28 x 128 -> 128,
+// 3x3, W2 70.0 -> 46.7 us; 64 x 28 x 28 x 160 -> 200, 1x1, signed W3 35.4 ->
+// 25.1 us; 4 x 14 x 14 x 96 -> 64, 5x5, W2 13.9 -> 13.9 us (host-bound).
 #pragma once
 
 #include <type_traits>
@@ -347,7 +354,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(96)))
 void conv_generic_kernel_tiled(const uint32_t* __restrict__ act,
                                const uint32_t* __restrict__ wts,
                                int32_t* __restrict__ out, TiledArgs g) {
-    static_assert(!XN || (A == 1 && W == 1), "+-1 data on both sides");
+    static_assert(!XN || A == 1, "+-1 activations");
     __shared__ uint32_t lds[kWaves * kTileWords];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -538,7 +545,7 @@ using TiledKernelFn = void (*)(const uint32_t*, const uint32_t*, int32_t*,
                                TiledArgs);
 
 // Kernel for A x W planes at a time, chunks of cb words, c channels per
-// accumulator tile (max_channels or 4).
+// accumulator tile (max_channels or 4); xnor: +-1 activations.
 template <int A>
 TiledKernelFn pick_a(int w, int cb, int c, bool xnor, bool req);
 template <> TiledKernelFn pick_a<1>(int, int, int, bool, bool);
@@ -571,7 +578,12 @@ TiledKernelFn pick_cb(int cb, int c, bool req) {
 template <int A>
 TiledKernelFn pick_for_a(int w, int cb, int c, bool xnor, bool req) {
     if constexpr (A == 1)
-        if (xnor) return pick_cb<1, 1, true>(cb, c, req);
+        if (xnor) switch (w) {
+                case 1: return pick_cb<1, 1, true>(cb, c, req);
+                case 2: return pick_cb<1, 2, true>(cb, c, req);
+                case 3: return pick_cb<1, 3, true>(cb, c, req);
+                default: return pick_cb<1, 4, true>(cb, c, req);
+            }
     switch (w) {
         case 1: return pick_cb<A, 1, false>(cb, c, req);
         case 2: return pick_cb<A, 2, false>(cb, c, req);

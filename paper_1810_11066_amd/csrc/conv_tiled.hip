@@ -55,8 +55,16 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     const int cw = (s.c + 31) / 32;
     pl.a = group_planes(s.abits);
     pl.w = group_planes(s.wbits);
-    const Encoding e = encoding_terms(s);
-    pl.xnor = e.xnor;
+    Encoding e = encoding_terms(s);
+    plane_weights(s.wbits, s.wenc, g.pw8);
+    pl.xnor = s.aenc == kBipolar && s.abits == 1;
+    if (pl.xnor && !e.xnor) {
+        // aw sum_j pw_j (2 S_j - SW_j) = aw sum_j pw_j (SA - D_j)
+        const int32_t aw = -e.csw;
+        e.cs = -aw;
+        for (int j = 0; j < s.wbits; ++j) e.csa += aw * g.pw8[j];
+        e.csw = 0;
+    }
     // words per chunk: 3 or 4, whichever reads fewer past the plane (4 when
     // equal: fewer steps)
     pl.cb = cw < 4 ? cw : ceil_div(cw, 3) * 3 < ceil_div(cw, 4) * 4 ? 3 : 4;
@@ -78,7 +86,6 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     g.pix_step = pix_step;
     g.ch_step = ch_step;
     plane_weights(s.abits, s.aenc, g.pa);
-    plane_weights(s.wbits, s.wenc, g.pw8);
     g.cs = e.cs; g.csa = e.csa; g.csw = e.csw; g.cn = e.cn;
     g.out_scale = rq ? rq->scale : 0.0f;
     g.out_bits = rq ? rq->bits : 0;

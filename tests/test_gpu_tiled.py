@@ -86,7 +86,8 @@ SHAPES = [
 ]
 BITS = [(1, 1, U, U), (2, 1, U, B), (1, 2, B, U), (1, 1, B, B), (2, 2, S, U),
         (2, 3, U, S), (3, 3, S, S), (4, 1, U, U), (1, 4, U, B), (4, 2, B, S),
-        (4, 4, B, B), (5, 3, U, U), (8, 1, S, B), (2, 7, U, S), (6, 6, S, B)]
+        (4, 4, B, B), (5, 3, U, U), (8, 1, S, B), (2, 7, U, S), (6, 6, S, B),
+        (1, 1, B, U), (1, 3, B, S), (1, 4, B, B), (1, 7, B, S)]
 
 
 @pytest.mark.parametrize("bits", BITS, ids=lambda b: "A%d%sW%d%s" % (
