@@ -40,10 +40,12 @@ UNITS = ([("api.hip", "api", ()), ("quant_pack.hip", "quant_pack", ()),
          ("dense_rows.hip", "dense_rows", ())] +
          [("conv_fast_inst.hip", "conv_fast_a%d" % a, ("BS_A=%d" % a,))
           for a in range(1, 5)] +
-         [("conv_pix_inst.hip", "conv_pix_a%d" % a,
-           ("BS_PIX_FAMILY=0", "BS_A=%d" % a)) for a in range(1, 5)] +
-         [("conv_pix_inst.hip", "conv_pix_s%d" % a,
-           ("BS_PIX_FAMILY=1", "BS_A=%d" % a)) for a in range(1, 5)] +
+         [("conv_pix_inst.hip", "conv_pix_a%d_%d" % (a, alone),
+           ("BS_PIX_FAMILY=0", "BS_A=%d" % a, "BS_ALONE=%d" % alone))
+          for a in range(1, 5) for alone in (0, 1)] +
+         [("conv_pix_inst.hip", "conv_pix_s%d_%d" % (a, alone),
+           ("BS_PIX_FAMILY=1", "BS_A=%d" % a, "BS_ALONE=%d" % alone))
+          for a in range(1, 5) for alone in (0, 1)] +
          [("conv_pix_inst.hip", "conv_pix_b", ("BS_PIX_FAMILY=2",))] +
          [("conv_tiled_inst.hip", "conv_tiled_a%d" % a, ("BS_A=%d" % a,))
           for a in range(1, 5)])

@@ -259,15 +259,15 @@ int64_t pix_images_per_launch(const ConvShape& s, bool req,
 // Pixels-on-lanes kernel for this shape, or nullptr.  src: where the
 // activations come from (pix::kSrcPacked, kSrcCodes, kSrcFloat); the staged
 // forms read whole 32-code words of each pixel, so they need c % 32 == 0.
-pix::PixKernelFn pix_kernel_for(const ConvShape& s, bool req, int src,
+pix::PixKernels pix_kernel_for(const ConvShape& s, bool req, int src,
                                 pix::PlanInfo* info, bool dual = false) {
     const int64_t cw = (s.c + 31) / 32;
-    if (s.abits > 4 || s.wbits > 4) return nullptr;
-    if (s.kh != s.kw || s.sh != s.sw) return nullptr;
+    if (s.abits > 4 || s.wbits > 4) return {};
+    if (s.kh != s.kw || s.sh != s.sw) return {};
     // output tiles are written in 16-byte quads of channels
-    if (s.oc % 4 != 0) return nullptr;
-    if (src != pix::kSrcPacked && s.c % 32 != 0) return nullptr;
-    if (pix_images_per_launch(s, req, src) < 1) return nullptr;
+    if (s.oc % 4 != 0) return {};
+    if (src != pix::kSrcPacked && s.c % 32 != 0) return {};
+    if (pix_images_per_launch(s, req, src) < 1) return {};
     return pix::pick(s.abits, s.wbits, s.aenc, s.wenc, s.kh, s.sh, (int)cw,
                      req, src, dual, info);
 }
@@ -312,6 +312,31 @@ int resident_blocks(pix::PixKernelFn fn, size_t lds) {
     std::lock_guard<std::mutex> lock(mu);
     cache.push_back({fn, dev, lds, blocks});
     return blocks;
+}
+
+// The kernel of a planned grid; int32_out: a plain call's int32 output.
+//
+// The one for lone waves where no SIMD gets a second wave, i.e. a CU a second
+// block (blocks are one wave per SIMD).  On either side of the line, kernel
+// for lone waves / for several: 16x16x128 -> 128 3x3 A2W2 at 1024 waves 5.0 /
+// 5.9 us, at 1152 waves 7.0 / 6.5; 16x16x64 -> 64 A4W4 7.4 / 9.2 and 11.3 /
+// 10.1; requantized 16x16x256 -> 256 A2W1 9.7 / 11.3 and 13.4 / 12.1.
+//
+// It also serves int32 results of few word pairs each, whose stores bound the
+// call: 64x56x56x32 -> 64 3x3 A1W1 (9 pairs) 14.4 / 17.2 us, 64x28x28x128 ->
+// 256 1x1 A2W1 (8 pairs) 11.9 / 13.1; at 18 pairs 64x56x56x32 -> 64 A2W1 21.4 /
+// 19.8, but where the pixel rows end within a 64-byte piece 32x28x28x32 -> 732
+// 29.3 / 33.1.  4-bit activations have 32 words of a pixel to 8 pairs and gain
+// from the other kernel (64x28x28x64 -> 256 1x1 A4W1 14.2 / 13.3 us).
+pix::PixKernelFn kernel_for_grid(const ConvShape& s, const pix::PixKernels& k,
+                                 const dim3& grid, bool int32_out) {
+    static_assert(pix::kWavesPerBlock == 4, "one wave per SIMD and block");
+    if ((int64_t)grid.x <= device_cus()) return k.alone;
+    const int64_t pairs = (int64_t)s.kh * s.kw * ((s.c + 31) / 32) * s.abits *
+                          s.wbits;
+    if (int32_out && s.abits <= 3 && pairs <= (s.oc % 16 ? 18 : 9))
+        return k.alone;
+    return k.fn;
 }
 
 // Largest input region, in pixels, that a block of a staged launch packs
@@ -570,11 +595,11 @@ struct Pair {
     float scale1;
 };
 
-// Launches the pixels-on-lanes kernel fn over the batch, in chunks of
+// Launches the pixels-on-lanes kernel k over the batch, in chunks of
 // pix_images_per_launch images (a single launch unless the tensors pass
 // 2 GB).  rq: requantized, bit-packed output (out holds uint32 words);
 // pair: the second output of a paired kernel, or nullptr.
-hipError_t launch_pix(const ConvShape& s, pix::PixKernelFn fn,
+hipError_t launch_pix(const ConvShape& s, const pix::PixKernels& k,
                       const uint32_t* act, const uint32_t* wts, int32_t* out,
                       int forced_run, const Requant* rq, hipStream_t st,
                       const Pair* pair = nullptr) {
@@ -598,7 +623,7 @@ hipError_t launch_pix(const ConvShape& s, pix::PixKernelFn fn,
         pix::PixArgs g;
         dim3 grid;
         size_t lds = 0;
-        plan_pix(c, fn, forced_run, rq, &g, &grid, &lds);
+        plan_pix(c, k.fn, forced_run, rq, &g, &grid, &lds);
         if (pair) {
             g.out1 = pair->out1 + n0 * out_img;
             g.out1_scale = pair->scale1;
@@ -609,7 +634,8 @@ hipError_t launch_pix(const ConvShape& s, pix::PixKernelFn fn,
         // kernels without a paired conv never read wts1
         const uint32_t* w1 = pair ? pair->wts1 : wts;
         const hipError_t e =
-            launch(fn, grid, dim3(pix::kBlock), lds, st, a, wts, w1, o, g);
+            launch(kernel_for_grid(c, k, grid, !rq && !pair), grid,
+                   dim3(pix::kBlock), lds, st, a, wts, w1, o, g);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -624,8 +650,8 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
                              float in_scale, const uint32_t* wts,
                              int32_t* out, int forced_run, hipStream_t st) {
     pix::PlanInfo info{};
-    const pix::PixKernelFn fn = pix_kernel_for(s, false, src, &info);
-    if (!fn) return hipErrorNotSupported;
+    const pix::PixKernels k = pix_kernel_for(s, false, src, &info);
+    if (!k) return hipErrorNotSupported;
     const int64_t per = pix_images_per_launch(s, false, src);
     struct Chunk {
         int64_t n0;
@@ -639,7 +665,7 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
         c.n = (int32_t)(s.n - n0 < per ? s.n - n0 : per);
         Chunk ch;
         ch.n0 = n0;
-        if (!plan_pix_staged(c, fn, forced_run, src, in_scale, &ch.g,
+        if (!plan_pix_staged(c, k.fn, forced_run, src, in_scale, &ch.g,
                              &ch.grid, &ch.lds))
             return hipErrorNotSupported;
         chunks.push_back(ch);
@@ -650,8 +676,9 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
         const uint32_t* a = reinterpret_cast<const uint32_t*>(
             static_cast<const uint8_t*>(act) + ch.n0 * in_img);
         int32_t* o = out + ch.n0 * out_img;
-        const hipError_t e = launch(fn, ch.grid, dim3(pix::kBlock), ch.lds, st,
-                                    a, wts, wts, o, ch.g);
+        const hipError_t e =
+            launch(kernel_for_grid(s, k, ch.grid, true), ch.grid,
+                   dim3(pix::kBlock), ch.lds, st, a, wts, wts, o, ch.g);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -695,7 +722,7 @@ bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
 // rows, pixels-on-lanes, the tiled generic kernel, then the plain one; 3 and 2
 // try only their own family (pixels- or channels-on-lanes) before the plain
 // generic kernel; 1 is that one only.
-Family choose(const ConvShape& s, int mode, pix::PixKernelFn* pfn,
+Family choose(const ConvShape& s, int mode, pix::PixKernels* pfn,
               pix::PlanInfo* info) {
     if (mode == 0 && rows::covers(s)) return Family::kRows;
     if (mode == 0 || mode == 3) {
@@ -714,7 +741,7 @@ hipError_t launch_conv(const ConvShape& s, const uint32_t* act,
                        const uint32_t* wts, int32_t* out,
                        const ConvOptions& opt, hipStream_t st) {
     const int mode = opt.mode;
-    pix::PixKernelFn pfn = nullptr;
+    pix::PixKernels pfn;
     pix::PlanInfo info{};
     dim3 grid;
     size_t lds = 0;
@@ -751,7 +778,7 @@ hipError_t launch_conv_requant(const ConvShape& s, const uint32_t* act,
     // the pixels-on-lanes kernel (modes 0 and 3), else the tiled generic
     // kernel (mode 0), else plain loops
     pix::PlanInfo info{};
-    pix::PixKernelFn pfn = nullptr;
+    pix::PixKernels pfn;
     if (opt.mode == 0 || opt.mode == 3)
         pfn = pix_kernel_for(s, true, pix::kSrcPacked, &info);
     if (pfn) {
@@ -798,7 +825,7 @@ hipError_t launch_conv_pair(const ConvShape& s, const uint32_t* act,
                             float scale1, const ConvOptions& opt,
                             hipStream_t st) {
     pix::PlanInfo info{};
-    pix::PixKernelFn fn = nullptr;
+    pix::PixKernels fn;
     if (opt.mode == 0 || opt.mode == 3)
         fn = pix_kernel_for(s, rq != nullptr, pix::kSrcPacked, &info, true);
     if (fn) {
@@ -857,7 +884,7 @@ int describe_conv_staged(const ConvShape& s, bool from_float,
                          const ConvOptions& opt, char* buf, size_t len) {
     const int src = from_float ? pix::kSrcFloat : pix::kSrcCodes;
     pix::PlanInfo info{};
-    const pix::PixKernelFn fn = pix_kernel_for(s, false, src, &info);
+    const pix::PixKernels fn = pix_kernel_for(s, false, src, &info);
     if (!fn) return -1;
     // the plan of the first launch (of `launches` image chunks)
     const int64_t per = pix_images_per_launch(s, false, src);
@@ -866,7 +893,7 @@ int describe_conv_staged(const ConvShape& s, bool from_float,
     pix::PixArgs g;
     dim3 grid;
     size_t lds = 0;
-    if (!plan_pix_staged(c, fn, opt.units_per_wave, src, 1.0f, &g, &grid,
+    if (!plan_pix_staged(c, fn.fn, opt.units_per_wave, src, 1.0f, &g, &grid,
                          &lds))
         return -1;
     const int64_t launches = (s.n + per - 1) / per;
@@ -876,18 +903,20 @@ int describe_conv_staged(const ConvShape& s, bool from_float,
                     "conv_pix_kernel<A=%d,W=%d,%s,K=%d,S=%d,CW=%d> "
                     "staged %s: patch=%dtaps x %dwords slice=%dch x "
                     "%dtaps grid=%u block=%d lds=%zu region=%dpx units=%d "
-                    "units_per_wave=%d%s",
+                    "units_per_wave=%d%s%s",
                     s.abits, s.wbits, kenc, s.kh, s.sh, (s.c + 31) / 32,
                     from_float ? "float32" : "codes",
                     info.tb, info.cb, info.ocb, info.ts, grid.x, pix::kBlock,
                     lds, g.region_pixels, g.units, g.per_wave,
+                    kernel_for_grid(s, fn, grid, true) != fn.fn
+                        ? " lone waves" : "",
                     launches > 1 ? " (per launch; batch split)" : "");
 }
 
 int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
                   size_t len) {
     const int mode = opt.mode;
-    pix::PixKernelFn pfn = nullptr;
+    pix::PixKernels pfn;
     pix::PlanInfo info{};
     dim3 grid;
     size_t lds = 0;
@@ -905,7 +934,8 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
             ConvShape c = s;
             c.n = (int32_t)(s.n < per ? s.n : per);
             pix::PixArgs g;
-            plan_pix(c, pfn, opt.units_per_wave, nullptr, &g, &grid, &lds);
+            plan_pix(c, pfn.fn, opt.units_per_wave, nullptr, &g, &grid,
+                     &lds);
             const int64_t launches = (s.n + per - 1) / per;
             char kenc[48];
             kernel_encodings(info, kenc, sizeof(kenc));
@@ -913,10 +943,12 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
                             "conv_pix_kernel<A=%d,W=%d,%s,K=%d,S=%d,CW=%d> "
                             "patch=%dtaps x %dwords slice=%dch x %dtaps "
                             "grid=%u block=%d lds=%zu units=%d "
-                            "units_per_wave=%d%s",
+                            "units_per_wave=%d%s%s",
                             s.abits, s.wbits, kenc, s.kh, s.sh, cw, info.tb,
                             info.cb, info.ocb, info.ts, grid.x, pix::kBlock,
                             lds, g.units, g.per_wave,
+                            kernel_for_grid(s, pfn, grid, true) != pfn.fn
+                                ? " lone waves" : "",
                             launches > 1 ? " (per launch; batch split)" : "");
         }
         case Family::kChannels: {

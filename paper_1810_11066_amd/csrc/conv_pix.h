@@ -142,27 +142,44 @@ __device__ __forceinline__ void bcnt_first(uint32_t& acc, uint32_t x) {
     asm("v_bcnt_u32_b32 %0, %1, 0" : "=v"(acc) : "v"(x));
 }
 
-// acc += popcount(a AND w) (first: acc = ..), w a uniform word.  The AND is
-// given its 64-bit encoding.  With the compiler's 32-bit one, streams of
-// 4-byte ANDs and 8-byte popcounts issued at 39.1 T lane-instructions/s (7
-// waves per SIMD); all-8-byte streams issue at 41.7 T, and every conv kernel
-// gains more than that: ResNet-18 layer 6 at batch 128 53.4 -> 47.1 us, layer
-// 9 56.2 -> 50.1 us, layer 2 at batch 64 30.8 -> 26.9 us, 3-bit codes on both
-// sides 128x28x28x128 -> 256 120.3 -> 106.8 us.  AND and popcount stand in
-// one asm block so that the pair stays together.  (A microbenchmark with an
-// s_nop in every pair reached 44-48 T, the kernels became 1-6 % slower with
-// it.)
+// acc += popcount(a AND w) (first: acc = ..), w a uniform word.
+//
+// With several waves on a SIMD the pair is one asm block (ALONE false): the
+// compiler puts an s_nop behind an asm block that writes a VGPR, and waves
+// whose AND, popcount, s_nop interleave issue more than streams without it.
+// The pair stream alone, in T lane-instructions/s at 1, 2, 3, 4 and 8 waves
+// per SIMD: with the s_nop 25, 48, 38, 49, 50; without 36, 37, 38, 38, 39.  (An
+// s_nop in every second pair gives 30, 40, 41, 42, 44, and the AND's 64-bit
+// encoding without any 29, 39, 40, 42, 44.)  ResNet-18 layer 6 at batch 128
+// 55.8 -> 50.0 us, layer 9 58.7 -> 53.3, layer 2 at batch 64 35.3 -> 31.5, 3-bit
+// codes on both sides 128x28x28x128 -> 256 122 -> 108 us.
+//
+// A wave that has its SIMD to itself loses the s_nop's slot: 16x16x16x64 -> 64
+// 3x3 (1024 waves) A4W4 7.4 -> 9.2 us, 8x16x16x128 -> 128 A3W3 8.9 -> 11.1 us.
+// Launches of so few waves take the kernel that leaves the pair to the
+// compiler (ALONE), which issues the AND of the next pair ahead of each
+// popcount.
+template <bool ALONE>
 __device__ __forceinline__ void and_bcnt_acc(uint32_t& acc, uint32_t a,
                                              uint32_t w) {
-    uint32_t x;
-    asm("v_and_b32_e64 %1, %2, %3\n\tv_bcnt_u32_b32 %0, %1, %0"
-        : "+v"(acc), "=&v"(x) : "s"(w), "v"(a));
+    if constexpr (ALONE) {
+        bcnt_acc(acc, a & w);
+    } else {
+        uint32_t x;
+        asm("v_and_b32_e64 %1, %2, %3\n\tv_bcnt_u32_b32 %0, %1, %0"
+            : "+v"(acc), "=&v"(x) : "s"(w), "v"(a));
+    }
 }
+template <bool ALONE>
 __device__ __forceinline__ void and_bcnt_first(uint32_t& acc, uint32_t a,
                                                uint32_t w) {
-    uint32_t x;
-    asm("v_and_b32_e64 %1, %2, %3\n\tv_bcnt_u32_b32 %0, %1, 0"
-        : "=&v"(acc), "=&v"(x) : "s"(w), "v"(a));
+    if constexpr (ALONE) {
+        bcnt_first(acc, a & w);
+    } else {
+        uint32_t x;
+        asm("v_and_b32_e64 %1, %2, %3\n\tv_bcnt_u32_b32 %0, %1, 0"
+            : "=&v"(acc), "=&v"(x) : "s"(w), "v"(a));
+    }
 }
 
 // Order this wave's LDS writes before its following LDS reads (and the reads
@@ -452,7 +469,7 @@ __device__ __forceinline__ void flush_tile(const uint32_t* __restrict__ tile,
 // words pc (A planes x CW words) and the channel's filter words f (W planes
 // x CW words, uniform), plus the bipolar-filter correction with lc1, the
 // plane-weighted popcount of pc.
-template <int A, int W, int E, int CW>
+template <int A, int W, int E, int CW, bool ALONE>
 __device__ __forceinline__ uint32_t centre_1x1(const uint32_t (&pc)[A][CW],
                                                const uint32_t* f,
                                                uint32_t lc1) {
@@ -468,10 +485,10 @@ __device__ __forceinline__ uint32_t centre_1x1(const uint32_t (&pc)[A][CW],
 #pragma unroll
             for (int i = 0; i < A; ++i) {
                 if (fresh[i + j]) {
-                    and_bcnt_first(acc[i + j], pc[i][c], f[j * CW + c]);
+                    and_bcnt_first<ALONE>(acc[i + j], pc[i][c], f[j * CW + c]);
                     fresh[i + j] = false;
                 } else {
-                    and_bcnt_acc(acc[i + j], pc[i][c], f[j * CW + c]);
+                    and_bcnt_acc<ALONE>(acc[i + j], pc[i][c], f[j * CW + c]);
                 }
             }
     uint32_t v = 0;
@@ -489,7 +506,7 @@ __device__ __forceinline__ uint32_t centre_1x1(const uint32_t (&pc)[A][CW],
 // or block's first slice; callers with nothing left pass any valid slice
 // address, so the load never needs a branch or a null check).  `patch` holds
 // the block's TB taps x A planes x CB words.
-template <int A, int W, int E, int K, int CW>
+template <int A, int W, int E, int K, int CW, bool ALONE>
 __device__ __forceinline__ void compute_quad(
     const uint32_t (&patch)[Plan<A, W, K, CW>::TB][A][Plan<A, W, K, CW>::CB],
     uint32_t lc, const TapInfo<A, W, K, CW>& tv, gu32* src, gu32* next,
@@ -574,9 +591,9 @@ __device__ __forceinline__ void compute_quad(
                                     else bcnt_acc(acc[o][s], x);
                                 } else {
                                     if (fresh[o][s])
-                                        and_bcnt_first(acc[o][s], a, wv);
+                                        and_bcnt_first<ALONE>(acc[o][s], a, wv);
                                     else
-                                        and_bcnt_acc(acc[o][s], a, wv);
+                                        and_bcnt_acc<ALONE>(acc[o][s], a, wv);
                                 }
                                 fresh[o][s] = false;
                             }
@@ -970,7 +987,7 @@ __device__ __forceinline__ int block_offset(int nb) {
 // (nb == 0) or added to (nb > 0) the lane's tile row.  On exit f[0] is
 // receiving `next_block` (the next block's first slice, or any valid slice
 // address when there is none).
-template <int A, int W, int E, int K, int S, int CW>
+template <int A, int W, int E, int K, int S, int CW, bool ALONE>
 __device__ __forceinline__ void run_block(
     const uint32_t (&patch)[Plan<A, W, K, CW>::TB][A][Plan<A, W, K, CW>::CB],
     gu32* src, int nq, int nb, gu32* next_block,
@@ -984,7 +1001,7 @@ __device__ __forceinline__ void run_block(
     for (int qi = 0; qi < nq; ++qi) {
         uint32_t val[4];
         gu32* q = src + (size_t)qi * 4 * Pl::FW;
-        compute_quad<A, W, E, K, CW>(
+        compute_quad<A, W, E, K, CW, ALONE>(
             patch, lc, tv, q, qi + 1 < nq ? q + 4 * Pl::FW : next_block, f,
             val);
         // only this lane touches its tile row until the flush
@@ -1052,8 +1069,9 @@ constexpr int min_waves_per_simd() {
 // (K-1)/2), over the same output grid and channels, with filters wts1 and
 // output g.out1 (whole patches only).  wts1 is a kernel argument, read-only
 // and unaliased like wts, so that its uniform loads may be scalar loads.
+// ALONE: for launches of at most one wave per SIMD (and_bcnt_acc).
 template <int A, int W, int E, int K, int S, int CW, bool REQ, int SRC,
-          bool DUAL>
+          bool DUAL, bool ALONE>
 __global__ __launch_bounds__(kBlock) __attribute__((
     amdgpu_num_sgpr(96),
     amdgpu_waves_per_eu(min_waves_per_simd<A, W, E, K, CW, REQ, DUAL>())))
@@ -1236,8 +1254,8 @@ void conv_pix_kernel(
                 for (int k = 0; k < F1; ++k) f1[k] = q1[k];
 #pragma unroll
                 for (int o = 0; o < 4; ++o) {
-                    put(o, centre_1x1<A, W, E, CW>(patch[kCentre],
-                                                   f1 + o * W * CW, lc1));
+                    put(o, centre_1x1<A, W, E, CW, ALONE>(
+                               patch[kCentre], f1 + o * W * CW, lc1));
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
@@ -1272,7 +1290,7 @@ void conv_pix_kernel(
             auto quad = [&](int qi) __attribute__((always_inline)) {
                 uint32_t val[4];
                 gu32* q = src + (size_t)qi * 4 * FW;
-                compute_quad<A, W, E, K, CW>(
+                compute_quad<A, W, E, K, CW, ALONE>(
                     patch, lc, tv, q, qi + 1 < nq ? q + 4 * FW : src, f, val);
                 if constexpr (REQ) {
                     // a packed byte holds 2 quads; runs start on a byte
@@ -1385,13 +1403,13 @@ void conv_pix_kernel(
 #pragma unroll 1
                     for (int nb = 0; nb < NB; nb += 2) {
                         if (nb + 1 < NB) load_block(pb, nb + 1);
-                        run_block<A, W, E, K, S, CW>(
+                        run_block<A, W, E, K, S, CW, ALONE>(
                             pa, blk(nb), nq, nb,
                             nb + 1 < NB ? blk(nb + 1) : qsrc, f, row, g, v.oy,
                             v.ox);
                         if (nb + 1 < NB) {
                             if (nb + 2 < NB) load_block(pa, nb + 2);
-                            run_block<A, W, E, K, S, CW>(
+                            run_block<A, W, E, K, S, CW, ALONE>(
                                 pb, blk(nb + 1), nq, nb + 1,
                                 nb + 2 < NB ? blk(nb + 2) : qsrc, f, row, g,
                                 v.oy, v.ox);
@@ -1402,7 +1420,7 @@ void conv_pix_kernel(
 #pragma unroll 1
                     for (int nb = 0; nb < NB; ++nb) {
                         load_block(pa, nb);
-                        run_block<A, W, E, K, S, CW>(
+                        run_block<A, W, E, K, S, CW, ALONE>(
                             pa, blk(nb), nq, nb,
                             nb + 1 < NB ? blk(nb + 1) : qsrc, f, row, g, v.oy,
                             v.ox);
@@ -1443,6 +1461,13 @@ struct PlanInfo {
     int nb;     // reduction blocks
 };
 
+// A specialisation's kernel, and the one for launches of at most one wave per
+// SIMD (and_bcnt_acc; the same kernel where the pairs are XORs).
+struct PixKernels {
+    PixKernelFn fn = nullptr, alone = nullptr;
+    explicit operator bool() const { return fn != nullptr; }
+};
+
 // Kernel for a supported (A, W, encodings, K, S, CW, requantized output) or
 // nullptr, with its plan (output channels per filter slice, taps per slice,
 // taps and words per plane of a reduction block).  ae / we are the operand
@@ -1455,37 +1480,38 @@ struct PlanInfo {
 //                      and signed activations with signed filters of the
 //                      same width, int32 output;
 //   pick_bipolar_act   +-1 activations with 1-bit filters, int32 output.
-// dual: the paired kernel that also computes the centre-tap 1x1 conv.
-PixKernelFn pick(int a, int w, int ae, int we, int k, int s, int cw, bool req,
-                 int src, bool dual, PlanInfo* info);
-template <int A>
+// dual: the paired kernel that also computes the centre-tap 1x1 conv.  ALONE:
+// the kernel for lone waves.
+PixKernels pick(int a, int w, int ae, int we, int k, int s, int cw, bool req,
+                int src, bool dual, PlanInfo* info);
+template <int A, bool ALONE>
 PixKernelFn pick_a(int w, bool b, int k, int s, int cw, bool req, int src,
                    bool dual, PlanInfo* info);
-template <> PixKernelFn pick_a<1>(int, bool, int, int, int, bool, int, bool,
-                                  PlanInfo*);
-template <> PixKernelFn pick_a<2>(int, bool, int, int, int, bool, int, bool,
-                                  PlanInfo*);
-template <> PixKernelFn pick_a<3>(int, bool, int, int, int, bool, int, bool,
-                                  PlanInfo*);
-template <> PixKernelFn pick_a<4>(int, bool, int, int, int, bool, int, bool,
-                                  PlanInfo*);
-template <int A>
+template <int A, bool ALONE>
 PixKernelFn pick_signed(int w, int ae, int we, int k, int s, int cw,
                         PlanInfo* info);
-template <> PixKernelFn pick_signed<1>(int, int, int, int, int, int, PlanInfo*);
-template <> PixKernelFn pick_signed<2>(int, int, int, int, int, int, PlanInfo*);
-template <> PixKernelFn pick_signed<3>(int, int, int, int, int, int, PlanInfo*);
-template <> PixKernelFn pick_signed<4>(int, int, int, int, int, int, PlanInfo*);
-PixKernelFn pick_bipolar_act(int we, int k, int s, int cw, PlanInfo* info);
+#define BS_DECLARE(A, ALONE)                                                  \
+    template <>                                                               \
+    PixKernelFn pick_a<A, ALONE>(int, bool, int, int, int, bool, int, bool,   \
+                                 PlanInfo*);                                  \
+    template <>                                                               \
+    PixKernelFn pick_signed<A, ALONE>(int, int, int, int, int, int, PlanInfo*);
+BS_DECLARE(1, false) BS_DECLARE(1, true)
+BS_DECLARE(2, false) BS_DECLARE(2, true)
+BS_DECLARE(3, false) BS_DECLARE(3, true)
+BS_DECLARE(4, false) BS_DECLARE(4, true)
+#undef BS_DECLARE
+PixKernelFn pick_bipolar_act(int we, int k, int s, int cw, bool alone,
+                             PlanInfo* info);
 
 // Specialisations (included by the sources above).  Requantizing variants
 // exist for unipolar activations with unipolar or bipolar filters only;
 // staged activations (src != kSrcPacked) for unipolar activations with
-// unipolar or bipolar filters, int32 output; paired kernels (dual) for unipolar activations with
-// unipolar or bipolar filters, 3x3 windows, whole patches, and at most 16
-// filter words per quad of the 1x1 conv (W CW <= 4), int32 or requantized
-// output.
-template <int A, int W, int E, int K, int S, int CW>
+// unipolar or bipolar filters, int32 output; paired kernels (dual) for
+// unipolar activations with unipolar or bipolar filters, 3x3 windows, whole
+// patches, and at most 16 filter words per quad of the 1x1 conv (W CW <= 4),
+// int32 or requantized output.
+template <int A, int W, int E, int K, int S, int CW, bool ALONE>
 PixKernelFn pick_kscw(bool req, int src, bool dual, PlanInfo* info) {
     using Pl = Plan<A, W, K, CW>;
     constexpr int UU = 3 * kUnipolar + kUnipolar, UB = 3 * kUnipolar + kBipolar;
@@ -1503,9 +1529,9 @@ PixKernelFn pick_kscw(bool req, int src, bool dual, PlanInfo* info) {
                           (E == UU || E == UB)) {
                 if (src != kSrcPacked) return nullptr;
                 return req ? conv_pix_kernel<A, W, E, K, S, CW, true,
-                                             kSrcPacked, true>
+                                             kSrcPacked, true, ALONE>
                            : conv_pix_kernel<A, W, E, K, S, CW, false,
-                                             kSrcPacked, true>;
+                                             kSrcPacked, true, ALONE>;
             } else {
                 return nullptr;
             }
@@ -1515,14 +1541,14 @@ PixKernelFn pick_kscw(bool req, int src, bool dual, PlanInfo* info) {
                 if (req) return nullptr;
                 if (src == kSrcCodes)
                     return conv_pix_kernel<A, W, E, K, S, CW, false,
-                                           kSrcCodes, false>;
+                                           kSrcCodes, false, ALONE>;
                 // float32 activations: 1x1 windows only (a 3x3 window's
                 // staging would read its float rows in one burst before
                 // any arithmetic, as long as a separate quantize + pack)
                 if constexpr (K == 1) {
                     if (src == kSrcFloat)
                         return conv_pix_kernel<A, W, E, K, S, CW, false,
-                                               kSrcFloat, false>;
+                                               kSrcFloat, false, ALONE>;
                 }
                 return nullptr;
             } else {
@@ -1531,80 +1557,88 @@ PixKernelFn pick_kscw(bool req, int src, bool dual, PlanInfo* info) {
         }
         if constexpr (E == UU || E == UB)
             return req ? conv_pix_kernel<A, W, E, K, S, CW, true, kSrcPacked,
-                                         false>
+                                         false, ALONE>
                        : conv_pix_kernel<A, W, E, K, S, CW, false, kSrcPacked,
-                                         false>;
+                                         false, ALONE>;
         else
             return req ? nullptr
                        : conv_pix_kernel<A, W, E, K, S, CW, false, kSrcPacked,
-                                         false>;
+                                         false, ALONE>;
     }
 }
 
 // Words per plane: 1..16 for 3x3 windows; 1x1 windows (and dense, a 1x1
 // conv) up to 128 words = 4096 input channels.
-template <int A, int W, int E, int K, int S>
+template <int A, int W, int E, int K, int S, bool ALONE>
 PixKernelFn pick_cw(int cw, bool req, int src, bool dual, PlanInfo* info) {
     switch (cw) {
-        case 1: return pick_kscw<A, W, E, K, S, 1>(req, src, dual, info);
-        case 2: return pick_kscw<A, W, E, K, S, 2>(req, src, dual, info);
-        case 4: return pick_kscw<A, W, E, K, S, 4>(req, src, dual, info);
-        case 8: return pick_kscw<A, W, E, K, S, 8>(req, src, dual, info);
-        case 16: return pick_kscw<A, W, E, K, S, 16>(req, src, dual, info);
+        case 1: return pick_kscw<A, W, E, K, S, 1, ALONE>(req, src, dual, info);
+        case 2: return pick_kscw<A, W, E, K, S, 2, ALONE>(req, src, dual, info);
+        case 4: return pick_kscw<A, W, E, K, S, 4, ALONE>(req, src, dual, info);
+        case 8: return pick_kscw<A, W, E, K, S, 8, ALONE>(req, src, dual, info);
+        case 16:
+            return pick_kscw<A, W, E, K, S, 16, ALONE>(req, src, dual,
+                                                       info);
         default: break;
     }
     if constexpr (K == 1) {
         switch (cw) {
-            case 32: return pick_kscw<A, W, E, K, S, 32>(req, src, dual, info);
-            case 64: return pick_kscw<A, W, E, K, S, 64>(req, src, dual, info);
+            case 32:
+                return pick_kscw<A, W, E, K, S, 32, ALONE>(req, src, dual,
+                                                           info);
+            case 64:
+                return pick_kscw<A, W, E, K, S, 64, ALONE>(req, src, dual,
+                                                           info);
             case 128:
-                return pick_kscw<A, W, E, K, S, 128>(req, src, dual, info);
+                return pick_kscw<A, W, E, K, S, 128, ALONE>(req, src, dual,
+                                                            info);
             default: break;
         }
     }
     return nullptr;
 }
 
-template <int A, int W, int E>
+template <int A, int W, int E, bool ALONE>
 PixKernelFn pick_ks(int k, int s, int cw, bool req, int src, bool dual,
                     PlanInfo* info) {
     if (k == 1)
-        return s == 1 ? pick_cw<A, W, E, 1, 1>(cw, req, src, dual, info)
-                      : pick_cw<A, W, E, 1, 2>(cw, req, src, dual, info);
+        return s == 1 ? pick_cw<A, W, E, 1, 1, ALONE>(cw, req, src, dual, info)
+                      : pick_cw<A, W, E, 1, 2, ALONE>(cw, req, src, dual, info);
     if (k == 3)
-        return s == 1 ? pick_cw<A, W, E, 3, 1>(cw, req, src, dual, info)
-                      : pick_cw<A, W, E, 3, 2>(cw, req, src, dual, info);
+        return s == 1 ? pick_cw<A, W, E, 3, 1, ALONE>(cw, req, src, dual, info)
+                      : pick_cw<A, W, E, 3, 2, ALONE>(cw, req, src, dual, info);
     return nullptr;
 }
 
 // Unipolar activations: every weight width 1..4 with unipolar weights;
 // bipolar weights at W = 1.
-template <int A>
+template <int A, bool ALONE>
 PixKernelFn pick_for_a(int w, bool b, int k, int s, int cw, bool req, int src,
                        bool dual, PlanInfo* info) {
     constexpr int UU = 3 * kUnipolar + kUnipolar, UB = 3 * kUnipolar + kBipolar;
-    if (b) return w == 1 ? pick_ks<A, 1, UB>(k, s, cw, req, src, dual, info)
-                         : nullptr;
+    if (b)
+        return w == 1 ? pick_ks<A, 1, UB, ALONE>(k, s, cw, req, src, dual, info)
+                      : nullptr;
     switch (w) {
-        case 1: return pick_ks<A, 1, UU>(k, s, cw, req, src, dual, info);
-        case 2: return pick_ks<A, 2, UU>(k, s, cw, req, src, dual, info);
-        case 3: return pick_ks<A, 3, UU>(k, s, cw, req, src, dual, info);
-        case 4: return pick_ks<A, 4, UU>(k, s, cw, req, src, dual, info);
+        case 1: return pick_ks<A, 1, UU, ALONE>(k, s, cw, req, src, dual, info);
+        case 2: return pick_ks<A, 2, UU, ALONE>(k, s, cw, req, src, dual, info);
+        case 3: return pick_ks<A, 3, UU, ALONE>(k, s, cw, req, src, dual, info);
+        case 4: return pick_ks<A, 4, UU, ALONE>(k, s, cw, req, src, dual, info);
         default: return nullptr;
     }
 }
 
 // Signed filters of width 2..4 with unipolar activations; signed
 // activations with signed filters of the same width.
-template <int A>
+template <int A, bool ALONE>
 PixKernelFn pick_signed_for_a(int w, int ae, int we, int k, int s, int cw,
                               PlanInfo* info) {
     constexpr int US = 3 * kUnipolar + kSigned, SS = 3 * kSigned + kSigned;
     if (we != kSigned) return nullptr;
     if (ae == kSigned) {
         if constexpr (A >= 2)
-            return w == A ? pick_ks<A, A, SS>(k, s, cw, false, kSrcPacked,
-                                              false, info)
+            return w == A ? pick_ks<A, A, SS, ALONE>(k, s, cw, false,
+                                                     kSrcPacked, false, info)
                           : nullptr;
         else
             return nullptr;
@@ -1612,13 +1646,13 @@ PixKernelFn pick_signed_for_a(int w, int ae, int we, int k, int s, int cw,
     if (ae != kUnipolar) return nullptr;
     switch (w) {
         case 2:
-            return pick_ks<A, 2, US>(k, s, cw, false, kSrcPacked, false,
+            return pick_ks<A, 2, US, ALONE>(k, s, cw, false, kSrcPacked, false,
                                       info);
         case 3:
-            return pick_ks<A, 3, US>(k, s, cw, false, kSrcPacked, false,
+            return pick_ks<A, 3, US, ALONE>(k, s, cw, false, kSrcPacked, false,
                                       info);
         case 4:
-            return pick_ks<A, 4, US>(k, s, cw, false, kSrcPacked, false,
+            return pick_ks<A, 4, US, ALONE>(k, s, cw, false, kSrcPacked, false,
                                       info);
         default: return nullptr;
     }

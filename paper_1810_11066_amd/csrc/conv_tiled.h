@@ -324,7 +324,8 @@ __device__ __forceinline__ void reduce(
                                                      p[i][k], keep[k],
                                                      fs.w[o][j][k]));
                             else
-                                pix::and_bcnt_acc(n, p[i][k], fs.w[o][j][k]);
+                                pix::and_bcnt_acc<false>(n, p[i][k],
+                                                         fs.w[o][j][k]);
                         }
             __builtin_amdgcn_sched_barrier(0);
         }

@@ -1,0 +1,56 @@
+"""The kernel each rule of the dispatch picks, on both sides of its lines, by
+the describe calls (host-side planning for 256 compute units, no GPU)."""
+import pytest
+
+from paper_1810_11066_amd import bitserial as bs
+
+U, B, S = bs.UNIPOLAR, bs.BIPOLAR, bs.SIGNED
+
+
+@pytest.fixture(autouse=True)
+def defaults():
+    bs.load_library()
+    yield
+    bs.bs_set_kernel_mode(0)
+    bs.bs_set_units_per_wave(0)
+
+
+def conv(n, h, w, c, oc, k, s, abits, wbits, aenc=U, wenc=U):
+    return bs.ConvParams(n, h, w, c, oc, k, k, s, s, k // 2, k // 2, abits,
+                         wbits, aenc, wenc)
+
+
+def dense(m, k, n, abits, wbits, aenc=U, wenc=U):
+    return conv(1, 1, m, k, n, 1, 1, abits, wbits, aenc, wenc)
+
+
+def family(p):
+    return bs.bs_conv2d_describe(p).split("_kernel")[0]
+
+
+def test_lone_waves():
+    """At most one wave per SIMD, a workgroup per CU: the kernel for lone
+    waves; one workgroup more: the kernel for several."""
+    bs.bs_set_units_per_wave(1)
+    for oc, lone in ((64, True), (68, False)):      # 1024 and 1088 units
+        d = bs.bs_conv2d_describe(conv(16, 16, 16, 64, oc, 3, 1, 2, 2))
+        assert d.startswith("conv_pix_kernel"), d
+        assert d.endswith(" lone waves") == lone, d
+    for oc, lone in ((64, True), (68, False)):
+        d = bs.bs_conv2d_codes_describe(conv(16, 16, 16, 64, oc, 3, 1, 2, 2))
+        assert d.endswith(" lone waves") == lone, d
+
+
+@pytest.mark.parametrize("c,oc,k,abits,wbits,lone", [
+    (32, 64, 3, 1, 1, True),       # 9 word pairs a result: stores bound it
+    (32, 64, 3, 2, 1, False),      # 18
+    (32, 732, 3, 2, 1, True),      # 18, rows end within a 64-byte piece
+    (64, 732, 3, 2, 1, False),     # 36
+    (128, 256, 1, 2, 1, True),     # 8
+    (64, 256, 1, 4, 1, False),     # 8, 4-bit activations
+])
+def test_store_bound_results(c, oc, k, abits, wbits, lone):
+    bs.bs_set_units_per_wave(1)
+    d = bs.bs_conv2d_describe(conv(64, 28, 28, c, oc, k, 1, abits, wbits))
+    assert d.startswith("conv_pix_kernel"), d
+    assert d.endswith(" lone waves") == lone, d
