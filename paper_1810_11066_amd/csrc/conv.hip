@@ -724,7 +724,7 @@ bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
 // generic kernel; 1 is that one only.
 Family choose(const ConvShape& s, int mode, pix::PixKernels* pfn,
               pix::PlanInfo* info) {
-    if (mode == 0 && rows::covers(s)) return Family::kRows;
+    if (mode == 0 && rows::covers(s, device_cus())) return Family::kRows;
     if (mode == 0 || mode == 3) {
         *pfn = pix_kernel_for(s, false, pix::kSrcPacked, info);
         if (*pfn && !(mode == 0 && tiled_is_faster(s, *info)))

@@ -6,7 +6,7 @@
 namespace bs {
 namespace rows {
 
-// Rows up to which the kernel serves a product of at least so many words per
+// Rows up to which the kernel may serve a product of at least so many words per
 // plane.  Measured per launch against the kernel that serves it otherwise
 // (n = 4096, k = 4096, A2W2): 1 row 4.2 against 13.1 us, 16 rows 6.1 against
 // 13.3, 32 rows 10.3 against 13.3, 48 rows 14.2 against 13.2; n = 1000, k =
@@ -16,8 +16,9 @@ namespace rows {
 constexpr int kFewRows = 16, kFewWords = 24;
 constexpr int kMoreRows = 32, kMoreWords = 96;
 
-// True for a matrix product (1x1, stride 1, no padding) the kernel serves.
-bool covers(const ConvShape& s);
+// True for a matrix product (1x1, stride 1, no padding) the kernel serves on a
+// device of cus compute units.
+bool covers(const ConvShape& s, int cus);
 
 hipError_t launch_rows(const ConvShape& s, const uint32_t* act,
                        const uint32_t* wts, int32_t* out, hipStream_t st);

@@ -236,6 +236,13 @@ Fn pick(int a, int w, int r, bool xnor) {
     }
 }
 
+// Rows of a wave's tile.
+int tile_rows(const ConvShape& s) {
+    return (int64_t)s.n * s.oh * s.ow <= 2
+               ? 1
+               : wide_rows(group_planes(s.abits), group_planes(s.wbits));
+}
+
 struct Plan {
     Fn fn;
     RowsArgs g;
@@ -264,7 +271,7 @@ Plan make_plan(const ConvShape& s) {
     plane_weights(s.abits, s.aenc, g.pa);
     plane_weights(s.wbits, s.wenc, g.pw);
     g.cs = e.cs; g.csa = e.csa; g.csw = e.csw; g.cn = e.cn;
-    pl.r = g.m <= 2 ? 1 : wide_rows(pl.a, pl.w);
+    pl.r = tile_rows(s);
     g.tiles_n = (g.n + kTileCols - 1) / kTileCols;
     g.tiles = g.tiles_n * ((g.m + pl.r - 1) / pl.r);
     g.div_tiles.init((uint32_t)g.tiles_n);
@@ -273,14 +280,38 @@ Plan make_plan(const ConvShape& s) {
     return pl;
 }
 
+// Waves per SIMD up to which the kernel is the faster one.  A wave's tile ends
+// with a cross-lane sum per output and reads each weight word for R rows only,
+// so with many tiles of short rows (large n) the kernels with pixels or output
+// channels on the lanes win.  Measured, this kernel / the best other one, at
+// 4 waves a SIMD and at 8: k = 768 A2W2 (16 rows, n = 4096, 8192) 5.0 / 4.8 and
+// 7.7 / 4.9 us, A4W4 (4 rows) 4.9 / 8.5 and 7.9 / 8.7; k = 2048 A2W2 5.1 / 5.5
+// and 7.9 / 6.8; k = 3072 A2W1 (32 rows, n = 6144 waves and 8192) 1.02 and 0.85
+// of the other's rate; k = 4096 A2W2 16 waves 13.6 / 16.0, 64 waves (32 rows, n
+// = 32768) 66.5 / 37.0.  One or two rows leave the other kernels' lanes idle:
+// k = 768, n = 32768 A2W2 4.3 / 4.5, n = 65536 6.9 / 5.1.
+int waves_per_simd(int m, int cw, int rows) {
+    if (m <= 2) return cw < 96 ? 8 : 64;
+    const bool wide = rows == 4;
+    if (cw < 64) return wide ? 2 : 4;
+    if (cw < 96) return wide ? 4 : 8;
+    if (cw < 128) return wide ? 6 : 12;
+    return wide && m > kFewRows ? 12 : 16;
+}
+
 }  // namespace
 
-bool covers(const ConvShape& s) {
+bool covers(const ConvShape& s, int cus) {
     if (s.kh != 1 || s.kw != 1 || s.sh != 1 || s.sw != 1 || s.ph || s.pw)
         return false;
     const int64_t m = (int64_t)s.n * s.oh * s.ow, cw = (s.c + 31) / 32;
     if (!(m <= kFewRows && cw >= kFewWords) &&
         !(m <= kMoreRows && cw >= kMoreWords))
+        return false;
+    const int r = tile_rows(s);
+    const int64_t waves =
+        (m + r - 1) / r * (((int64_t)s.oc + kTileCols - 1) / kTileCols);
+    if (waves > (int64_t)waves_per_simd((int)m, (int)cw, r) * 4 * cus)
         return false;
     // popcounts are folded as 24-bit values
     if (s.c >= 1 << 23) return false;

@@ -54,3 +54,23 @@ def test_store_bound_results(c, oc, k, abits, wbits, lone):
     d = bs.bs_conv2d_describe(conv(64, 28, 28, c, oc, k, 1, abits, wbits))
     assert d.startswith("conv_pix_kernel"), d
     assert d.endswith(" lone waves") == lone, d
+
+
+@pytest.mark.parametrize("m,k,n,abits,wbits,rows", [
+    # waves of 4 rows x 4 columns (A W <= 4): 2, 4, 6, 12 or 16 per SIMD
+    (16, 1024, 2048, 2, 2, True), (16, 1024, 2052, 2, 2, False),
+    (16, 2048, 4096, 2, 2, True), (16, 2048, 4100, 2, 2, False),
+    (32, 3072, 3072, 2, 1, True), (32, 3072, 3076, 2, 1, False),
+    (32, 4096, 6144, 1, 1, True), (32, 4096, 6148, 1, 1, False),
+    (16, 4096, 16384, 2, 2, True), (16, 4096, 16388, 2, 2, False),
+    # waves of one row x 4 columns: 4, 8, 12 or 16
+    (16, 768, 1024, 4, 4, True), (16, 768, 1028, 4, 4, False),
+    (16, 768, 50000, 4, 4, False), (32, 4096, 2048, 8, 8, True),
+    (32, 4096, 2052, 8, 8, False),
+    # one row: 8, 64
+    (1, 768, 32768, 2, 2, True), (1, 768, 32772, 2, 2, False),
+    (1, 4096, 65536, 2, 2, True),
+    # rows and words as before
+    (17, 1024, 64, 2, 2, False), (16, 704, 64, 2, 2, False)])
+def test_few_rows(m, k, n, abits, wbits, rows):
+    assert (family(dense(m, k, n, abits, wbits)) == "dense_rows") == rows
