@@ -689,33 +689,53 @@ enum class Family { kPixels, kChannels, kTiled, kRows, kGeneric };
 // Shapes the tiled kernel serves faster than a pixel kernel that walks a long
 // reduction in blocks (nb > 1).  Units are 64 pixels x 4 channels.
 //
-// Few units, at most 3 per CU, so that most SIMDs have none or one wave: the
-// tiled kernel's waves share a unit's reduction.  Per launch, pixel kernel /
-// tiled: 7x7x512 -> 512 3x3 at batch 1 (128 units) A2W1 11.2 / 6.5, A3W3 34.7 /
-// 13.4 us, at batch 4 (512 units) 11.8 / 7.4 and 35.1 / 15.1, at batch 16 (1664
-// units) 16.2 / 17.9 and 38.6 / 39.5.  Products with 512 columns, k = 4096: 256
-// rows (512 units) A2W2 16.6 / 11.9, A4W4 54.8 / 24.0 us; 512 rows (1024
-// units) 16.9 / 19.2 and 55.4 / 41.4.  Problems of fewer than 16 units, which
-// were not measured, stay with the pixel kernel.
+// Few units, so that most SIMDs have none or one wave: the tiled kernel's
+// waves share a unit's reduction.  Up to 3 units per CU for 3x3 windows (7x7x512
+// -> 512, pixel kernel / tiled: 128 units A2W1 9.4 / 6.3, A3W3 26.1 / 12.9 us;
+// 640 units A2W1 10.1 / 8.8, A3W3 28.7 / 21.2), where neighbouring lanes share
+// the words they load.  1x1 windows and products do not share them, and from 2
+// units per CU the tiled kernel is bound by those loads unless several filter
+// planes meet a word (k = 4096, 512 columns: 512 units A2W2 13.7 / 11.9, A4W4
+// 43.9 / 27.2 but A2W1 9.7 / 10.8, A4W1 17.0 / 20.3; 640 units A2W2 13.9 / 15.5,
+// A4W4 43.8 / 37.0; 256 units A2W1 9.6 / 7.3, A4W1 16.6 / 11.7), or the words are
+// few (k = 1024, 512 units, A2W1 4.6 / 4.2).  One bit on both sides gains up
+// to 1 unit per CU (512 units 6.4 / 6.7 us, 128 units 6.1 / 5.8), short
+// reductions nowhere (14x14x512 -> 512 1x1, 512 units: A2W2 3.9 / 4.5).  Problems
+// of fewer than 16 units stay with the pixel kernel, and so do those above the
+// lines (896 units of 3x3 A4W4 48.3 / 38.3).
 //
 // One unit per wave in a full round (12 to 28 units per CU) with multi-bit
 // activations and 1-bit filters: a wave then loads A words per popcount chain
 // for 4 channels only, and the loads (9 TB/s from the L2s) take longer than
 // the arithmetic, while a tiled wave's 16 channels share them.  7x7x512 -> 512
-// at batch 64 (6272 units) 50.8 / 37.0 us, 9x9x512 -> 128 at batch 128 (5184)
-// 45.3 / 28.2, 256 x 4096 x 4096 (4096) 32.4 / 22.8; 9x9x512 -> 128 at batch
+// at batch 64 (6272 units) A2 55.7 / 41.5 us, 256 x 4096 x 4096 (4096) A2 35.3 /
+// 24.8, A3 50.6 / 37.0, A4 66.6 / 45.2; below the line, 9x9x512 -> 128 at batch
 // 64 (2592) 23.9 / 27.9.  A1W1 18.3 / 24.3 and A2W2 58.6 / 68.7 us on the first
-// of these shapes stay with the pixel kernel.
+// of these shapes stay with the pixel kernel, and so do 3x3 windows of 8 words
+// at stride 1 up to 3 bits (14x14x256 -> 256 at batch 32, A2 21.3 / 23.5, A3 28.3
+// / 30.8), 3-bit 3x3 windows above 20 units per CU (7x7x512 -> 512 at batch 64
+// 53.0 / 55.1, at batch 40 34.6 / 31.8), and 1x1 windows of 16 words (28x28x512 ->
+// 128 at batch 16, A3 8.3 / 11.0, A4 13.1 / 13.8).
 bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
     if (info.nb < 2) return false;
     const int64_t units =
         ((int64_t)s.n * s.oh * s.ow + 63) / 64 * (s.oc / 4);
     const int64_t cus = device_cus();
-    if (!((units >= 16 && units <= 3 * cus) ||
-          (s.wbits == 1 && s.abits >= 2 && units >= 12 * cus &&
-           units <= pix::kWavesPerSimd * 4 * cus)))
-        return false;
-    return tiled::covers(s, false);
+    const int a = s.abits, aw = s.abits * s.wbits, taps = s.kh * s.kw;
+    const int red = taps * ((s.c + 31) / 32);       // words per plane
+    int most = 0;                                   // units per CU
+    if (red < 32 || a * red < 64) most = 0;
+    else if (aw == 1) most = 1;
+    else if (taps == 1 && s.wbits == 1) most = a * red <= 128 ? 2 : 1;
+    else if (taps == 1) most = aw >= 16 ? 3 : 2;
+    else most = a == 1 && red < 128 ? 1 : 3;
+    const bool few = units >= 16 && units <= most * cus;
+    const bool loads = taps == 1 ? red >= 32
+                       : red >= 128 ? a != 3 || units <= 20 * cus
+                                    : a == 4 || s.sh > 1;
+    const bool round = s.wbits == 1 && a >= 2 && loads && units >= 12 * cus &&
+                       units <= pix::kWavesPerSimd * 4 * cus;
+    return (few || round) && tiled::covers(s, false);
 }
 
 // The kernel family a call takes: mode 0 tries the kernel for products of few

@@ -74,3 +74,29 @@ def test_store_bound_results(c, oc, k, abits, wbits, lone):
     (17, 1024, 64, 2, 2, False), (16, 704, 64, 2, 2, False)])
 def test_few_rows(m, k, n, abits, wbits, rows):
     assert (family(dense(m, k, n, abits, wbits)) == "dense_rows") == rows
+
+
+@pytest.mark.parametrize("p,tiled", [
+    # few units of 64 pixels x 4 channels
+    (conv(1, 7, 7, 512, 512, 3, 1, 1, 1), True),          # 128
+    (conv(4, 7, 7, 512, 512, 3, 1, 1, 1), False),         # 512
+    (conv(6, 7, 7, 512, 512, 3, 1, 2, 1), True),          # 640
+    (conv(8, 7, 7, 512, 512, 3, 1, 2, 1), False),         # 896
+    (conv(1, 14, 14, 512, 512, 1, 1, 2, 2), False),       # 16 words
+    (dense(256, 4096, 512, 2, 1), False),                 # 512, products
+    (dense(256, 4096, 256, 2, 1), True),                  # 256
+    (dense(256, 1024, 512, 2, 1), True),                  # 512, 32 words
+    (dense(256, 4096, 512, 2, 2), True),
+    (dense(320, 4096, 512, 2, 2), False),                 # 640
+    (dense(320, 4096, 512, 4, 4), True),
+    # one unit per wave in a full round
+    (conv(64, 7, 7, 512, 512, 3, 1, 2, 1), True),
+    (conv(32, 14, 14, 256, 256, 3, 1, 2, 1), False),      # 8 words
+    (conv(64, 14, 14, 256, 256, 3, 2, 2, 1), True),
+    (conv(64, 7, 7, 512, 512, 3, 1, 3, 1), False),        # 24.5 units per CU
+    (conv(40, 7, 7, 512, 512, 3, 1, 3, 1), True),         # 15.5
+    (dense(1792, 1024, 1024, 2, 1), True),
+    (conv(16, 28, 28, 512, 128, 1, 1, 3, 1), False)])     # 16 words
+def test_long_reductions(p, tiled):
+    assert family(p) == ("conv_generic" if tiled else "conv_pix")
+    assert ("tiled" in bs.bs_conv2d_describe(p)) == tiled

@@ -155,9 +155,9 @@ def test_dense_few_rows(oracle, m, n, k):
     ((2, 9, 9, 512, 1028, 3, 1), 3, 3, False),
     ((1, 1, 200, 4096, 64, 1, 1), 2, 2, True),
     # one unit per wave in a full round (3072 to 7168 units), A >= 2, W = 1
-    ((4, 14, 14, 256, 944, 3, 1), 2, 1, False),
-    ((4, 14, 14, 256, 948, 3, 1), 2, 1, True),
-    ((4, 14, 14, 256, 948, 3, 1), 1, 1, False),
+    ((4, 7, 7, 512, 3068, 3, 1), 2, 1, False),
+    ((4, 7, 7, 512, 3072, 3, 1), 2, 1, True),
+    ((4, 7, 7, 512, 3072, 3, 1), 1, 1, False),
     ((1, 1, 64 * 28, 1024, 1024, 1, 1), 2, 1, True),
     ((1, 1, 64 * 28 + 1, 1024, 1024, 1, 1), 2, 1, False)])
 def test_rule_for_long_reductions(oracle, shape, abits, wbits, tiled):
