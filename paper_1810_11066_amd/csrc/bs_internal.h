@@ -272,7 +272,7 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
 int describe_conv_staged(const ConvShape& s, bool from_float,
                          const ConvOptions& opt, char* buf, size_t len);
 
-// True when the channels-on-lanes kernel (mode 2) covers the shape.
+// True when the channels-on-lanes kernel covers the shape.
 bool conv_has_fast_path(const ConvShape& s);
 
 }  // namespace bs

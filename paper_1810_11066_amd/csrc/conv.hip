@@ -19,16 +19,17 @@
 //                      output channel oc0 + l, the wave walks groups of P
 //                      output pixels of one row; activation words are uniform
 //                      across the wave (scalar loads), filter words of the
-//                      block's 64 channels are staged once in LDS.  Kernel
-//                      mode 2 only: the tiled kernel is faster on its shapes.
+//                      block's 64 channels are staged once in LDS.  Serves
+//                      reductions of 2 to 4 words (and kernel mode 2).
 // conv_generic_kernel_tiled  pixels on lanes with a run-time window, stride,
 //                      channel count, bit-widths and encodings
 //                      (conv_tiled.h); serves what the pixel kernel does not.
 // dense_rows_kernel    the reduction on the lanes (dense_rows.hip), for matrix
 //                      products of few rows.
 // conv_generic_kernel  one output per thread, runtime everything; serves
-//                      every remaining shape (a single image or a filter set
-//                      past 2 GiB) and kernel mode 1.
+//                      reductions of one word with few outputs, every
+//                      remaining shape (a single image or a filter set past
+//                      2 GiB) and kernel mode 1.
 //
 // In the fast families the inner loop is one v_and_b32 (SGPR x VGPR) and one
 // accumulating v_bcnt_u32_b32 per word pair; the shift-add (and bipolar
@@ -738,10 +739,47 @@ bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
     return (few || round) && tiled::covers(s, false);
 }
 
+// Short reductions without a pixel kernel, where the tiled kernel's set-up per
+// wave (about 250 vector instructions) outweighs the products.
+//
+// Channels on lanes, up to 4 words per plane: one or two bits a pair of codes,
+// until its 64-channel blocks pass 64 Ki lanes per CU (16 Ki where most of a
+// block's lanes idle); 2 words also for blocks without idle lanes, whatever
+// their number, except at 3 to 8 bits a pair.  Channels-on-lanes / tiled: 128 Ki
+// outputs of 66 channels, 2 words, A2W1 2.5 / 3.3 us, 2 Mi 5.2 / 7.0, 6 Mi 10.7
+// / 11.0; 4 words A1W1 2 Mi 6.5 / 7.1, 6 Mi 13.9 / 10.4; 10 channels, 2 words,
+// A2W1 128 Ki 2.7 / 3.3, 512 Ki 4.1 / 4.0; 402 channels, 2 words, 6 Mi A4W4 30.4
+// / 34.8, A2W2 14.7 / 13.4.
+bool channels_are_faster(const ConvShape& s) {
+    const int64_t red = (int64_t)s.kh * s.kw * ((s.c + 31) / 32);
+    if (red > 4 || !conv_has_fast_path(s)) return false;
+    const int64_t aw = (int64_t)s.abits * s.wbits;
+    const int64_t lanes = ((int64_t)s.oc + 63) / 64 * 64;
+    const bool full = 9 * (int64_t)s.oc >= 8 * lanes;
+    if (red <= 2 && full && (aw <= 2 || aw >= 9)) return true;
+    return aw <= 2 && (int64_t)s.n * s.oh * s.ow * lanes <=
+                          (s.oc >= 32 ? 16384 : 4096) * (int64_t)device_cus();
+}
+
+// One output per thread, for one word per plane while there are at most 3 waves
+// of outputs per SIMD (2 above 9 bits a pair).  Plain / tiled: 64 Ki outputs
+// A1W1 2.5 / 3.0 us, A4W4 4.0 / 4.3, A5W5 4.8 / 7.4, A8W8 10.2 / 8.8; 128 Ki A1W1
+// 2.6 / 3.1, A3W3 3.5 / 3.9, A4W4 4.6 / 4.4; 158 Ki A2W2 3.3 / 3.9; 256 Ki A2W2
+// 3.6 / 3.6, A3W3 4.3 / 4.0.  At 2 words the two are within 0.4 us up to 64 Ki
+// outputs (A1W1 2.7 / 3.1, A2W2 3.5 / 3.6, A3W3 4.4 / 4.1) and the tiled kernel
+// serves them.
+bool plain_is_faster(const ConvShape& s) {
+    const int aw = s.abits * s.wbits;
+    return (int64_t)s.kh * s.kw * ((s.c + 31) / 32) == 1 && aw < 64 &&
+           (int64_t)s.n * s.oh * s.ow * s.oc <=
+               (aw <= 9 ? 768 : 512) * (int64_t)device_cus();
+}
+
 // The kernel family a call takes: mode 0 tries the kernel for products of few
-// rows, pixels-on-lanes, the tiled generic kernel, then the plain one; 3 and 2
-// try only their own family (pixels- or channels-on-lanes) before the plain
-// generic kernel; 1 is that one only.
+// rows, pixels-on-lanes, channels-on-lanes and the plain kernel for short
+// reductions, the tiled generic kernel, then the plain one; 3 and 2 try only
+// their own family (pixels- or channels-on-lanes) before the plain generic
+// kernel; 1 is that one only.
 Family choose(const ConvShape& s, int mode, pix::PixKernels* pfn,
               pix::PlanInfo* info) {
     if (mode == 0 && rows::covers(s, device_cus())) return Family::kRows;
@@ -751,6 +789,8 @@ Family choose(const ConvShape& s, int mode, pix::PixKernels* pfn,
             return Family::kPixels;
     }
     if (mode == 2 && conv_has_fast_path(s)) return Family::kChannels;
+    if (mode == 0 && !*pfn && channels_are_faster(s)) return Family::kChannels;
+    if (mode == 0 && !*pfn && plain_is_faster(s)) return Family::kGeneric;
     if (mode == 0 && tiled::covers(s, false)) return Family::kTiled;
     return *pfn ? Family::kPixels : Family::kGeneric;
 }

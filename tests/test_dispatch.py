@@ -100,3 +100,26 @@ def test_few_rows(m, k, n, abits, wbits, rows):
 def test_long_reductions(p, tiled):
     assert family(p) == ("conv_generic" if tiled else "conv_pix")
     assert ("tiled" in bs.bs_conv2d_describe(p)) == tiled
+
+
+@pytest.mark.parametrize("p,kernel", [
+    # 2 and 4 words per plane: channels on lanes
+    (dense(1900, 64, 66, 2, 1, U, B), "conv_ocl_kernel"),
+    (dense(32768, 64, 66, 2, 1, U, B), "conv_ocl_kernel"),    # 64 Ki lanes a CU
+    (dense(32769, 64, 66, 2, 1, U, B), "conv_generic_kernel_tiled"),
+    (dense(16384, 64, 10, 2, 1, U, B), "conv_ocl_kernel"),
+    (dense(16385, 64, 10, 2, 1, U, B), "conv_generic_kernel_tiled"),
+    (dense(15000, 64, 402, 4, 4, U, B), "conv_ocl_kernel"),
+    (dense(15000, 64, 402, 2, 2, U, B), "conv_generic_kernel_tiled"),
+    (dense(1900, 64, 66, 4, 4, U, B), "conv_generic_kernel_tiled"),
+    (dense(1900, 128, 66, 2, 1, U, B), "conv_ocl_kernel"),
+    (dense(1900, 192, 66, 2, 1, U, B), "conv_generic_kernel_tiled"),
+    # one word: one output per thread, up to 192 Ki or 128 Ki outputs
+    (dense(3072, 32, 64, 2, 2, S, U), "conv_generic_kernel A"),
+    (dense(3073, 32, 64, 2, 2, S, U), "conv_generic_kernel_tiled"),
+    (dense(2048, 32, 64, 4, 4, S, U), "conv_generic_kernel A"),
+    (dense(2049, 32, 64, 4, 4, S, U), "conv_generic_kernel_tiled"),
+    (dense(64, 32, 64, 8, 8, S, U), "conv_generic_kernel_tiled"),
+    (dense(64, 64, 64, 2, 2, S, U), "conv_generic_kernel_tiled")])
+def test_short_reductions(p, kernel):
+    assert bs.bs_conv2d_describe(p).startswith(kernel)
