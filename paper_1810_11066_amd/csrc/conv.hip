@@ -779,19 +779,25 @@ bool plain_is_faster(const ConvShape& s) {
 // rows, pixels-on-lanes, channels-on-lanes and the plain kernel for short
 // reductions, the tiled generic kernel, then the plain one; 3 and 2 try only
 // their own family (pixels- or channels-on-lanes) before the plain generic
-// kernel; 1 is that one only.
-Family choose(const ConvShape& s, int mode, pix::PixKernels* pfn,
-              pix::PlanInfo* info) {
-    if (mode == 0 && rows::covers(s, device_cus())) return Family::kRows;
+// kernel; 1 is that one only.  A run length set for the pixels-on-lanes kernel
+// keeps mode 0 on it wherever it exists.
+Family choose(const ConvShape& s, const ConvOptions& opt,
+              pix::PixKernels* pfn, pix::PlanInfo* info) {
+    const int mode = opt.mode;
+    const bool forced = opt.units_per_wave > 0;
+    if (mode == 0 && !forced && rows::covers(s, device_cus()))
+        return Family::kRows;
     if (mode == 0 || mode == 3) {
         *pfn = pix_kernel_for(s, false, pix::kSrcPacked, info);
-        if (*pfn && !(mode == 0 && tiled_is_faster(s, *info)))
+        if (*pfn && (mode == 3 || forced || !tiled_is_faster(s, *info)))
             return Family::kPixels;
     }
     if (mode == 2 && conv_has_fast_path(s)) return Family::kChannels;
-    if (mode == 0 && !*pfn && channels_are_faster(s)) return Family::kChannels;
-    if (mode == 0 && !*pfn && plain_is_faster(s)) return Family::kGeneric;
-    if (mode == 0 && tiled::covers(s, false)) return Family::kTiled;
+    if (mode != 0) return Family::kGeneric;
+    if (forced && rows::covers(s, device_cus())) return Family::kRows;
+    if (!*pfn && channels_are_faster(s)) return Family::kChannels;
+    if (!*pfn && plain_is_faster(s)) return Family::kGeneric;
+    if (tiled::covers(s, false)) return Family::kTiled;
     return *pfn ? Family::kPixels : Family::kGeneric;
 }
 
@@ -800,12 +806,11 @@ Family choose(const ConvShape& s, int mode, pix::PixKernels* pfn,
 hipError_t launch_conv(const ConvShape& s, const uint32_t* act,
                        const uint32_t* wts, int32_t* out,
                        const ConvOptions& opt, hipStream_t st) {
-    const int mode = opt.mode;
     pix::PixKernels pfn;
     pix::PlanInfo info{};
     dim3 grid;
     size_t lds = 0;
-    switch (choose(s, mode, &pfn, &info)) {
+    switch (choose(s, opt, &pfn, &info)) {
         case Family::kPixels:
             return launch_pix(s, pfn, act, wts, out, opt.units_per_wave,
                               nullptr, st);
@@ -975,7 +980,6 @@ int describe_conv_staged(const ConvShape& s, bool from_float,
 
 int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
                   size_t len) {
-    const int mode = opt.mode;
     pix::PixKernels pfn;
     pix::PlanInfo info{};
     dim3 grid;
@@ -987,7 +991,7 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
         snprintf(enc, sizeof(enc), "%s", names[s.wenc]);
     else
         snprintf(enc, sizeof(enc), "%s x %s", names[s.aenc], names[s.wenc]);
-    switch (choose(s, mode, &pfn, &info)) {
+    switch (choose(s, opt, &pfn, &info)) {
         case Family::kPixels: {
             // the plan of the first launch (of `launches` image chunks)
             const int64_t per = pix_images_per_launch(s, false);

@@ -123,3 +123,21 @@ def test_long_reductions(p, tiled):
     (dense(64, 64, 64, 2, 2, S, U), "conv_generic_kernel_tiled")])
 def test_short_reductions(p, kernel):
     assert bs.bs_conv2d_describe(p).startswith(kernel)
+
+
+def test_run_length_keeps_the_pixel_kernel():
+    """A run length set for the pixels-on-lanes kernel is used in mode 0 on
+    every shape that has one."""
+    for p in (conv(1, 7, 7, 512, 512, 3, 1, 2, 1), dense(256, 4096, 256, 2, 2),
+              dense(16, 1024, 512, 2, 2), conv(64, 7, 7, 512, 512, 3, 1, 2, 1)):
+        assert family(p) != "conv_pix"
+        bs.bs_set_units_per_wave(3)
+        d = bs.bs_conv2d_describe(p)
+        assert d.startswith("conv_pix_kernel") and "units_per_wave=3" in d
+        bs.bs_set_units_per_wave(0)
+    # none here: the call keeps its kernel
+    for p in (dense(16, 800, 64, 2, 2), conv(1, 9, 9, 96, 10, 3, 1, 2, 1)):
+        before = bs.bs_conv2d_describe(p)
+        bs.bs_set_units_per_wave(3)
+        assert bs.bs_conv2d_describe(p) == before
+        bs.bs_set_units_per_wave(0)
