@@ -784,17 +784,15 @@ bool plain_is_faster(const ConvShape& s) {
 Family choose(const ConvShape& s, const ConvOptions& opt,
               pix::PixKernels* pfn, pix::PlanInfo* info) {
     const int mode = opt.mode;
-    const bool forced = opt.units_per_wave > 0;
-    if (mode == 0 && !forced && rows::covers(s, device_cus()))
-        return Family::kRows;
-    if (mode == 0 || mode == 3) {
+    if (mode == 0 || mode == 3)
         *pfn = pix_kernel_for(s, false, pix::kSrcPacked, info);
-        if (*pfn && (mode == 3 || forced || !tiled_is_faster(s, *info)))
-            return Family::kPixels;
-    }
+    if (mode == 3) return *pfn ? Family::kPixels : Family::kGeneric;
     if (mode == 2 && conv_has_fast_path(s)) return Family::kChannels;
     if (mode != 0) return Family::kGeneric;
-    if (forced && rows::covers(s, device_cus())) return Family::kRows;
+    if (*pfn && opt.units_per_wave > 0) return Family::kPixels;
+    const bool pixel = *pfn && !tiled_is_faster(s, *info);
+    if (rows::covers(s, device_cus(), pixel)) return Family::kRows;
+    if (pixel) return Family::kPixels;
     if (!*pfn && channels_are_faster(s)) return Family::kChannels;
     if (!*pfn && plain_is_faster(s)) return Family::kGeneric;
     if (tiled::covers(s, false)) return Family::kTiled;

@@ -17,8 +17,9 @@ constexpr int kFewRows = 16, kFewWords = 24;
 constexpr int kMoreRows = 32, kMoreWords = 96;
 
 // True for a matrix product (1x1, stride 1, no padding) the kernel serves on a
-// device of cus compute units.
-bool covers(const ConvShape& s, int cus);
+// device of cus compute units; pixel: the pixel kernel would serve it otherwise
+// (the tiled kernel, if not).
+bool covers(const ConvShape& s, int cus, bool pixel);
 
 hipError_t launch_rows(const ConvShape& s, const uint32_t* act,
                        const uint32_t* wts, int32_t* out, hipStream_t st);

@@ -283,25 +283,44 @@ Plan make_plan(const ConvShape& s) {
 // Waves per SIMD up to which the kernel is the faster one.  A wave's tile ends
 // with a cross-lane sum per output and reads each weight word for R rows only,
 // so with many tiles of short rows (large n) the kernels with pixels or output
-// channels on the lanes win.  Measured, this kernel / the best other one, at
-// 4 waves a SIMD and at 8: k = 768 A2W2 (16 rows, n = 4096, 8192) 5.0 / 4.8 and
-// 7.7 / 4.9 us, A4W4 (4 rows) 4.9 / 8.5 and 7.9 / 8.7; k = 2048 A2W2 5.1 / 5.5
-// and 7.9 / 6.8; k = 3072 A2W1 (32 rows, n = 6144 waves and 8192) 1.02 and 0.85
-// of the other's rate; k = 4096 A2W2 16 waves 13.6 / 16.0, 64 waves (32 rows, n
-// = 32768) 66.5 / 37.0.  One or two rows leave the other kernels' lanes idle:
-// k = 768, n = 32768 A2W2 4.3 / 4.5, n = 65536 6.9 / 5.1.
-int waves_per_simd(int m, int cw, int rows) {
-    if (m <= 2) return cw < 96 ? 8 : 64;
+// channels on the lanes win.
+//
+// pixel: the pixel kernel would serve the call.  It leaves most lanes idle and
+// takes as long for 1 row as for 64, so the rows count.  Rate against it, at
+// waves per SIMD: k = 1024, 16 rows, A2W2 1.23 at 2, 0.93 at 4, A4W4 1.45 at 8,
+// 0.85 at 16; 9 rows A2W2 1.09 at 3, A4W4 1.32 at 9, 1.10 at 36; 8 rows A2W2 1.23
+// at 32; one bit a pair, 8 rows, 0.98 at 2, 0.94 at 4; k = 2048, 16 rows, one bit
+// 1.06 at 4, 0.97 at 8, A2W1 1.09 at 32; k = 4096, 32 rows, one bit 1.02 at 12,
+// 0.88 at 16, A2W1 1.12 at 16, 0.88 at 64, A4W4 1.23 at 32, 1.00 at 64; 24 rows,
+// one bit 1.01 at 24, 0.87 at 48, A4W4 1.21 at 96.
+//
+// Otherwise the tiled kernel would, with the output channels on the lanes: k =
+// 768, 16 rows, A2W2 1.25 at 2, 0.96 at 4, 0.63 at 8, A4W4 1.10 at 8, 0.65 at 16;
+// k = 1024, A8W8 1.25 at 4.5, 0.85 at 8; k = 3072, 32 rows, A2W1 1.02 at 6, 0.85
+// at 8, A4W4 1.46 at 8, 0.94 at 17; k = 4096 A8W8 1.13 at 17, 0.91 at 24.  One row
+// leaves its lanes idle: k = 768 A2W2 1.04 at 8, 0.74 at 16.
+int waves_per_simd(const ConvShape& s, int m, int cw, int rows, bool pixel) {
+    constexpr int kAny = 1 << 20;
     const bool wide = rows == 4;
-    if (cw < 64) return wide ? 2 : 4;
+    if (pixel) {
+        if (s.abits * s.wbits == 1)
+            return m <= 4 ? kAny : cw < 64 ? 2 : cw < 128 ? 4
+                                 : m > 24 ? 12 : m > kFewRows ? 24 : kAny;
+        if (m <= (wide ? 8 : 10)) return kAny;
+        if (cw < 64) return wide ? 3 : 8;
+        if (m <= (wide ? kFewRows : 24)) return kAny;
+        return wide ? 32 : 64;
+    }
+    if (m <= 2) return cw < 96 ? 8 : 64;
+    if (cw < 64) return wide ? 2 : cw < 32 ? 8 : 6;
     if (cw < 96) return wide ? 4 : 8;
     if (cw < 128) return wide ? 6 : 12;
-    return wide && m > kFewRows ? 12 : 16;
+    return !wide ? 20 : m > kFewRows ? 12 : 16;
 }
 
 }  // namespace
 
-bool covers(const ConvShape& s, int cus) {
+bool covers(const ConvShape& s, int cus, bool pixel) {
     if (s.kh != 1 || s.kw != 1 || s.sh != 1 || s.sw != 1 || s.ph || s.pw)
         return false;
     const int64_t m = (int64_t)s.n * s.oh * s.ow, cw = (s.c + 31) / 32;
@@ -311,7 +330,8 @@ bool covers(const ConvShape& s, int cus) {
     const int r = tile_rows(s);
     const int64_t waves =
         (m + r - 1) / r * (((int64_t)s.oc + kTileCols - 1) / kTileCols);
-    if (waves > (int64_t)waves_per_simd((int)m, (int)cw, r) * 4 * cus)
+    if (waves >
+        (int64_t)waves_per_simd(s, (int)m, (int)cw, r, pixel) * 4 * cus)
         return false;
     // popcounts are folded as 24-bit values
     if (s.c >= 1 << 23) return false;

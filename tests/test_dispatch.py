@@ -57,16 +57,28 @@ def test_store_bound_results(c, oc, k, abits, wbits, lone):
 
 
 @pytest.mark.parametrize("m,k,n,abits,wbits,rows", [
-    # waves of 4 rows x 4 columns (A W <= 4): 2, 4, 6, 12 or 16 per SIMD
-    (16, 1024, 2048, 2, 2, True), (16, 1024, 2052, 2, 2, False),
-    (16, 2048, 4096, 2, 2, True), (16, 2048, 4100, 2, 2, False),
+    # waves per SIMD of 4 rows x 4 columns (A W <= 4) or of one row, against
+    # the pixel kernel: 3 (8 of one row), any up to 8 (10) rows
+    (16, 1024, 3072, 2, 2, True), (16, 1024, 3076, 2, 2, False),
+    (8, 1024, 65536, 2, 2, True), (11, 1024, 4096, 4, 4, False),
+    (10, 1024, 65536, 4, 4, True), (16, 2048, 65536, 2, 2, True),
+    # one bit a pair: 2 and 4 from 5 rows on, 24 and 12
+    (8, 1024, 4096, 1, 1, True), (8, 1024, 4100, 1, 1, False),
+    (4, 1024, 65536, 1, 1, True), (16, 2048, 4096, 1, 1, True),
+    (16, 2048, 4100, 1, 1, False), (32, 4096, 6144, 1, 1, True),
+    (32, 4096, 6148, 1, 1, False), (24, 4096, 16384, 1, 1, True),
+    (24, 4096, 16388, 1, 1, False), (16, 4096, 65536, 1, 1, True),
+    # 32 rows: 32 and 64
+    (32, 4096, 16384, 2, 2, True), (32, 4096, 16388, 2, 2, False),
+    (32, 4096, 4096, 4, 4, True), (32, 4096, 8192, 4, 4, True),
+    (32, 4096, 8196, 4, 4, False), (24, 4096, 65536, 4, 4, True),
+    # against the tiled kernel: 2, 8 or 6, 6 and 20
+    (16, 768, 2048, 2, 2, True), (16, 768, 2052, 2, 2, False),
+    (16, 768, 2048, 4, 4, True), (16, 768, 2052, 4, 4, False),
+    (16, 1024, 1536, 8, 8, True), (16, 1024, 1540, 8, 8, False),
     (32, 3072, 3072, 2, 1, True), (32, 3072, 3076, 2, 1, False),
-    (32, 4096, 6144, 1, 1, True), (32, 4096, 6148, 1, 1, False),
-    (16, 4096, 16384, 2, 2, True), (16, 4096, 16388, 2, 2, False),
-    # waves of one row x 4 columns: 4, 8, 12 or 16
-    (16, 768, 1024, 4, 4, True), (16, 768, 1028, 4, 4, False),
-    (16, 768, 50000, 4, 4, False), (32, 4096, 2048, 8, 8, True),
-    (32, 4096, 2052, 8, 8, False),
+    (16, 768, 50000, 4, 4, False), (32, 4096, 2560, 8, 8, True),
+    (32, 4096, 2564, 8, 8, False),
     # one row: 8, 64
     (1, 768, 32768, 2, 2, True), (1, 768, 32772, 2, 2, False),
     (1, 4096, 65536, 2, 2, True),
