@@ -175,14 +175,20 @@ __global__ __launch_bounds__(kBlock) void pack_dpp_kernel(
 // chunk (one load of 4 or 1 bytes per lane) in flight and a 64-bit division
 // for each, 104749 rows of 101 floats took 27.9 us (now 12.2 us, 3.7 TB/s) and
 // 4096 rows of 1000 floats 10.4 us (now 5.4 us).  WIDE: 64-bit chunk numbers.
+//
+// A wave of few chunks takes one: its serial ballots count until the waves of
+// one chunk each are 6 on a SIMD.  One / eight chunks per wave: 1000 rows of 100
+// codes (2000 chunks) at 8 bits 2.6 / 3.3 us, 5000 chunks 3.0 / 3.2, 8192 3.4 /
+// 3.2, 16384 4.7 / 3.7; floats at 2 bits 2000 chunks 2.4 / 2.7, 8192 3.0 / 2.7.
 constexpr int kChunks = 8;
+constexpr int64_t kFewChunks = 6144;
 
 // old with `lane` (uniform) set to the uniform value (v_writelane_b32; the
 // compiler has no builtin for it)
 extern "C" __device__ int bs_writelane(int value, int lane, int old) __asm(
     "llvm.amdgcn.writelane.i32");
 
-template <bool FROM_FLOAT, int ENC, bool WIDE>
+template <bool FROM_FLOAT, int ENC, bool WIDE, int CHUNKS>
 __global__ __launch_bounds__(kBlock) void pack_ballot_kernel(
     const void* __restrict__ src, uint32_t* __restrict__ packed, int64_t k,
     int64_t nchunks, int64_t total, FastDiv div_chunks, int bits, float scale,
@@ -201,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void pack_ballot_kernel(
         if constexpr (WIDE) return chunk / nc;
         else return (Index)div_chunks.div((uint32_t)chunk);
     };
-    for (Index first = wave * kChunks; first < end; first += nwaves * kChunks) {
+    for (Index first = wave * CHUNKS; first < end; first += nwaves * CHUNKS) {
         const Index row = row_of(first);
         Index c = first - row * nc;
         // every chunk starts where the one before it ends, so the buffer is
@@ -210,12 +216,12 @@ __global__ __launch_bounds__(kBlock) void pack_ballot_kernel(
         const __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint8_t*>(static_cast<const uint8_t*>(src)) +
                 ((int64_t)row * k + (int64_t)c * 64) * kSize,
-            (short)0, 64 * kChunks * kSize, 0x00020000);
-        uint32_t raw[kChunks], code[kChunks];
-        int count[kChunks];
+            (short)0, 64 * CHUNKS * kSize, 0x00020000);
+        uint32_t raw[CHUNKS], code[CHUNKS];
+        int count[CHUNKS];
         uint32_t at = 0;
 #pragma unroll
-        for (int u = 0; u < kChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             const int64_t left = k - (int64_t)c * 64;
             const int n = first + u < end ? (left < 64 ? (int)left : 64) : 0;
             const uint32_t off =
@@ -231,7 +237,7 @@ __global__ __launch_bounds__(kBlock) void pack_ballot_kernel(
             if (++c == nc) c = 0;
         }
 #pragma unroll
-        for (int u = 0; u < kChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             code[u] = raw[u];
             if constexpr (FROM_FLOAT) {
                 code[u] = code_of<ENC>(__builtin_bit_cast(float, raw[u]),
@@ -245,12 +251,12 @@ __global__ __launch_bounds__(kBlock) void pack_ballot_kernel(
         const Index mine = first + (lane >> 1);
         const Index mrow = row_of(mine < end ? mine : first);
         const int64_t t = 2 * ((int64_t)mine - (int64_t)mrow * nc) + (lane & 1);
-        const bool stores = lane < 2 * kChunks && mine < end && t < kw;
+        const bool stores = lane < 2 * CHUNKS && mine < end && t < kw;
         uint32_t* dst = packed + (int64_t)mrow * bits * kw + t;
         for (int b = 0; b < bits; ++b) {
             uint32_t word = 0;
 #pragma unroll
-            for (int u = 0; u < kChunks; ++u) {
+            for (int u = 0; u < CHUNKS; ++u) {
                 const uint64_t m = __ballot((code[u] >> b) & 1u);
                 word = (uint32_t)bs_writelane((int)(uint32_t)m, 2 * u,
                                               (int)word);
@@ -517,23 +523,35 @@ hipError_t launch_qpack(const float* x, uint32_t* packed, uint32_t nwords,
                   nwords, d, scale, qmax);
 }
 
-// Any k: kChunks chunks of 64 elements per wave, 4 waves per block.
+template <bool FROM_FLOAT, int ENC, int CHUNKS>
+hipError_t launch_chunks(const void* src, uint32_t* packed, int64_t k,
+                         int64_t total, int bits, float scale, float qmax,
+                         hipStream_t st) {
+    const int64_t nchunks = (k + 63) / 64;
+    const dim3 grid(grid_for(total, 4 * CHUNKS));
+    FastDiv d{};
+    // the last step past the end stays within 32 bits
+    if (total > INT32_MAX - (int64_t)kMaxBlocks * 4 * CHUNKS)
+        return launch(pack_ballot_kernel<FROM_FLOAT, ENC, true, CHUNKS>, grid,
+                      dim3(kBlock), 0, st, src, packed, k, nchunks, total, d,
+                      bits, scale, qmax);
+    d.init((uint32_t)nchunks);
+    return launch(pack_ballot_kernel<FROM_FLOAT, ENC, false, CHUNKS>, grid,
+                  dim3(kBlock), 0, st, src, packed, k, nchunks, total, d, bits,
+                  scale, qmax);
+}
+
+// Any k, 4 waves per block.
 template <bool FROM_FLOAT, int ENC>
 hipError_t launch_ballot(const void* src, uint32_t* packed, int64_t rows,
                          int64_t k, int bits, float scale, float qmax,
                          hipStream_t st) {
-    const int64_t nchunks = (k + 63) / 64, total = rows * nchunks;
-    const dim3 grid(grid_for(total, 4 * kChunks));
-    FastDiv d{};
-    // the last step past the end stays within 32 bits
-    if (total > INT32_MAX - (int64_t)kMaxBlocks * 4 * kChunks)
-        return launch(pack_ballot_kernel<FROM_FLOAT, ENC, true>, grid,
-                      dim3(kBlock), 0, st, src, packed, k, nchunks, total, d,
-                      bits, scale, qmax);
-    d.init((uint32_t)nchunks);
-    return launch(pack_ballot_kernel<FROM_FLOAT, ENC, false>, grid,
-                  dim3(kBlock), 0, st, src, packed, k, nchunks, total, d, bits,
-                  scale, qmax);
+    const int64_t total = rows * ((k + 63) / 64);
+    if (total <= kFewChunks)
+        return launch_chunks<FROM_FLOAT, ENC, 1>(src, packed, k, total, bits,
+                                                 scale, qmax, st);
+    return launch_chunks<FROM_FLOAT, ENC, kChunks>(src, packed, k, total, bits,
+                                                   scale, qmax, st);
 }
 
 }  // namespace

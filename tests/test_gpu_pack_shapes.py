@@ -142,3 +142,25 @@ def test_more_than_2_31_chunks():
     for a in range(0, rows, 1 << 28):
         b = min(rows, a + (1 << 28))
         assert torch.equal(out[a:b], (q[a:b] & 1).int())
+
+
+@pytest.mark.parametrize("rows,k", [(2048, 165), (6144, 33), (6145, 33),
+                                    (3000, 70)])
+@pytest.mark.parametrize("bits", [1, 4, 8])
+def test_chunks_per_wave(oracle, rows, k, bits):
+    """Up to 6144 chunks a wave takes one, above it eight: codes and floats on
+    both sides."""
+    rng = np.random.default_rng(rows + k)
+    q = rng.integers(0, 256, size=(rows, k), dtype=np.uint8)
+    say("pack", rows, k, bits)
+    want = oracle.pack(q, bits)
+    g = Guarded(want.size)
+    bs.bs_pack(dev(q), g.t, rows, k, bits)
+    assert np.array_equal(g.words().reshape(want.shape), want)
+    x = rng.standard_normal((rows, k), dtype=np.float32) * 100
+    for enc in (bs.UNIPOLAR, bs.BIPOLAR if bits == 1 else bs.SIGNED):
+        say("quantize_pack", rows, k, enc, bits)
+        want = oracle.pack(oracle.quantize(x, 0.7, bits, enc), bits)
+        g = Guarded(want.size)
+        bs.bs_quantize_pack(dev(x), g.t, rows, k, 0.7, bits, enc)
+        assert np.array_equal(g.words().reshape(want.shape), want)
