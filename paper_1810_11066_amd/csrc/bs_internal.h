@@ -272,6 +272,9 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
 int describe_conv_staged(const ConvShape& s, bool from_float,
                          const ConvOptions& opt, char* buf, size_t len);
 
+// Compute units of the current device (cached per device).
+int device_cus();
+
 // True when the channels-on-lanes kernel covers the shape.
 bool conv_has_fast_path(const ConvShape& s);
 

@@ -336,8 +336,11 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_dpp_kernel(
 // layout puts them.
 //
 // A workgroup takes a tile of 256 V / TT rows x TT words (TT a power of two up
-// to 8, at most the words per plane) and stores it through LDS, so that
-// consecutive lanes store consecutive words of the packed rows.
+// to 8, or 64 where a row's codes are contiguous, at most the words per plane)
+// and stores it through LDS, so that consecutive lanes store consecutive words
+// of the packed rows; they do without it where a row's codes are contiguous,
+// and for BMK with one word per plane and row (1000 x 4096 contiguous codes at 8
+// bits, BMK, 10.4 us, with LDS 11.4; 64 x 3 x 12544 at 4 bits 9.8, with LDS 12.2).
 //
 // Bound by memory latency at small sizes and by the loads otherwise: with the
 // loads waited for one by one, every bit moved by an extract and a shift-or
@@ -378,8 +381,15 @@ __global__ __launch_bounds__(kBlock) void pack_strided_kernel(
     const int by_row = bmk ? lines : row_words;
     const int by_plane = bmk ? tile_rows << tt_log2 : mkb ? 1 : lines;
     const int by_word = mkb ? g.bits : 1;
-    const int qi = threadIdx.x & (threads_i - 1);
-    const int tt = threadIdx.x / threads_i;
+    // neighbouring threads take neighbouring rows, or words where the codes of
+    // a row are contiguous
+    const bool along = g.inner == 1;
+    const int qi = along ? threadIdx.x >> tt_log2
+                         : threadIdx.x & (threads_i - 1);
+    const int tt = along ? threadIdx.x & (lines - 1) : threadIdx.x / threads_i;
+    // consecutive threads hold consecutive words of a plane, or whole words of
+    // it `bits` apart: stored without LDS
+    const bool direct = along || (bmk && g.kw == 1);
     // outer index and first row of group n of V rows
     auto locate = [&](int64_t n, int64_t* o) -> int64_t {
         if constexpr (WIDE) *o = n / g.iv;
@@ -446,6 +456,18 @@ __global__ __launch_bounds__(kBlock) void pack_strided_kernel(
             // previous group's
             const int at = (int)(o * g.inner + i0 - r0);
             const int skip = (int)(want - i0);
+            if (direct) {
+                const int64_t row = o * g.inner + i0;
+                uint32_t* dst =
+                    packed + (mkb ? (row * g.kw + t) * g.bits
+                                  : row * g.kw + t);
+                const int64_t by_b = mkb ? 1 : g.rows * g.kw;
+                for (int b = 0; b < g.bits; ++b, dst += by_b)
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        if (v >= skip) dst[v] = plane_word(d[v], b);
+                continue;
+            }
             for (int b = 0; b < g.bits; ++b)
 #pragma unroll
                 for (int v = 0; v < V; ++v)
@@ -453,6 +475,7 @@ __global__ __launch_bounds__(kBlock) void pack_strided_kernel(
                         lds[strided_slot((at + v) * by_row + b * by_plane +
                                          tt * by_word)] = plane_word(d[v], b);
         }
+        if (direct) continue;
         __syncthreads();
         // the tile's words, at the same order in memory: rows of row_words
         // words every kw * bits (MBK: pieces of TT words every kw)
@@ -460,15 +483,15 @@ __global__ __launch_bounds__(kBlock) void pack_strided_kernel(
         const int words = left_t < lines ? (int)left_t : lines;
         const int64_t t0 = tw << tt_log2;
         if (bmk) {
-            for (int b = 0; b < g.bits; ++b) {
-                uint32_t* dst = packed + ((int64_t)b * g.rows + r0) * g.kw + t0;
-                for (int e = threadIdx.x; e < rows_here << tt_log2;
-                     e += kBlock) {
-                    const int w = e & (lines - 1);
-                    if (w < words)
-                        dst[(int64_t)(e >> tt_log2) * g.kw + w] =
-                            lds[strided_slot(b * by_plane + e)];
-                }
+            constexpr int PLANE = kBlock * V;      // words of a tile's plane
+            uint32_t* dst = packed + r0 * g.kw + t0;
+#pragma unroll 4
+            for (int e = threadIdx.x; e < g.bits * PLANE; e += kBlock) {
+                const int b = e / PLANE, r = (e % PLANE) >> tt_log2;
+                const int w = e & (lines - 1);
+                if (r < rows_here && w < words)
+                    dst[((int64_t)b * g.rows + r) * g.kw + w] =
+                        lds[strided_slot(e)];
             }
         } else if (words == g.kw && words == lines) {
             // whole rows: one contiguous piece of memory
@@ -606,7 +629,8 @@ static hipError_t launch_strided(const uint8_t* q, uint32_t* packed,
     g.k = k;
     g.inner = inner;
     g.kw = (k + 31) / 32;
-    while (g.tt_log2 < 3 && 2 << g.tt_log2 <= g.kw) ++g.tt_log2;
+    const int most = inner == 1 ? 6 : 3;
+    while (g.tt_log2 < most && 2 << g.tt_log2 <= g.kw) ++g.tt_log2;
     g.iv = (inner + V - 1) / V;
     g.groups = outer * g.iv;
     g.tiles_t = (g.kw + (1 << g.tt_log2) - 1) >> g.tt_log2;
@@ -634,11 +658,18 @@ hipError_t launch_pack_ex(const uint8_t* q, uint32_t* packed, int64_t outer,
                           hipStream_t st) {
     if (inner == 1 && layout == kLayoutMBK)
         return launch_pack(q, packed, outer, k, bits, st);
-    // four rows to a thread wherever a row's neighbours exist
-    return inner >= 4 ? launch_strided<4>(q, packed, outer, k, inner, bits,
-                                          layout, st)
-                      : launch_strided<1>(q, packed, outer, k, inner, bits,
-                                          layout, st);
+    // four rows to a thread wherever a row's neighbours exist and the grid
+    // keeps a workgroup for every other CU (workgroups of 4 x 256 rows x
+    // words); below that a thread's serial work counts: 8 bits, one row / four:
+    // 64 x 512 x 9 codes (12 workgroups) 6.4 / 11.2 us, 128 x 512 x 49 (104) 7.2 /
+    // 11.4, 64 x 128 x 196 (49) 4.4 / 6.1; 64 x 3 x 12544 (784) 21.3 / 18.7
+    const int64_t blocks =
+        outer * ((inner + 3) / 4) * ((k + 31) / 32) / kBlock;
+    return inner >= 4 && 2 * blocks >= device_cus()
+               ? launch_strided<4>(q, packed, outer, k, inner, bits, layout,
+                                   st)
+               : launch_strided<1>(q, packed, outer, k, inner, bits, layout,
+                                   st);
 }
 
 namespace {

@@ -164,3 +164,22 @@ def test_chunks_per_wave(oracle, rows, k, bits):
         g = Guarded(want.size)
         bs.bs_quantize_pack(dev(x), g.t, rows, k, 0.7, bits, enc)
         assert np.array_equal(g.words().reshape(want.shape), want)
+
+
+# one and four rows to a thread (128 workgroups of four), one word per plane
+# and row stored without LDS, tiles of up to 64 words along contiguous codes
+@pytest.mark.parametrize("shape", [
+    (127, 256, 128), (128, 256, 128), (130, 250, 129), (64, 3, 12544),
+    (9, 3, 1001), (2000, 31, 17), (64, 4096, 1), (50, 2070, 1), (700, 64, 1),
+    (33, 1000, 1)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("bits", [1, 3, 8])
+def test_pack_strided_tiles(oracle, shape, layout, bits):
+    outer, k, inner = shape
+    rng = np.random.default_rng(outer + k + inner)
+    q = rng.integers(0, 256, size=shape, dtype=np.uint8)
+    say("pack_ex", shape, layout, bits)
+    want = oracle.pack_ex(q, bits, axis=1, layout=layout)
+    g = Guarded(want.size)
+    bs.bs_pack_ex(dev(q), g.t, outer, k, inner, bits, layout)
+    assert np.array_equal(g.words().reshape(want.shape), want)
