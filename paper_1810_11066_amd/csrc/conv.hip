@@ -202,19 +202,6 @@ int pick_group_pixels(int ow) { return ow % 7 == 0 ? 7 : 8; }
 
 }  // namespace
 
-int device_cus() {
-    static std::atomic<int> cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int v = cache[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount,
-                              dev) != hipSuccess || v < 1)
-        v = 256;
-    cache[dev].store(v, std::memory_order_relaxed);
-    return v;
-}
-
 bool conv_has_fast_path(const ConvShape& s) {
     const int64_t cw = (s.c + 31) / 32;
     const int p = pick_group_pixels(s.ow);
@@ -284,6 +271,20 @@ pix::PixKernels pix_kernel_for(const ConvShape& s, bool req, int src,
     if (pix_images_per_launch(s, req, src) < 1) return {};
     return pix::pick(s.abits, s.wbits, s.aenc, s.wenc, s.kh, s.sh, (int)cw,
                      req, src, dual, info);
+}
+
+// Compute units of the current device (cached per device).
+int device_cus() {
+    static std::atomic<int> cache[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int v = cache[dev].load(std::memory_order_relaxed);
+    if (v > 0) return v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount,
+                              dev) != hipSuccess || v < 1)
+        v = 256;
+    cache[dev].store(v, std::memory_order_relaxed);
+    return v;
 }
 
 // Resident blocks of fn per CU (register, LDS and wave-slot limits), cached
