@@ -202,6 +202,19 @@ int pick_group_pixels(int ow) { return ow % 7 == 0 ? 7 : 8; }
 
 }  // namespace
 
+int device_cus() {
+    static std::atomic<int> cache[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int v = cache[dev].load(std::memory_order_relaxed);
+    if (v > 0) return v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount,
+                              dev) != hipSuccess || v < 1)
+        v = 256;
+    cache[dev].store(v, std::memory_order_relaxed);
+    return v;
+}
+
 bool conv_has_fast_path(const ConvShape& s) {
     const int64_t cw = (s.c + 31) / 32;
     const int p = pick_group_pixels(s.ow);
@@ -271,20 +284,6 @@ pix::PixKernels pix_kernel_for(const ConvShape& s, bool req, int src,
     if (pix_images_per_launch(s, req, src) < 1) return {};
     return pix::pick(s.abits, s.wbits, s.aenc, s.wenc, s.kh, s.sh, (int)cw,
                      req, src, dual, info);
-}
-
-// Compute units of the current device (cached per device).
-int device_cus() {
-    static std::atomic<int> cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int v = cache[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount,
-                              dev) != hipSuccess || v < 1)
-        v = 256;
-    cache[dev].store(v, std::memory_order_relaxed);
-    return v;
 }
 
 // Resident blocks of fn per CU (register, LDS and wave-slot limits), cached
@@ -456,10 +455,13 @@ void plan_pix_lds(const ConvShape& s, pix::PixKernelFn fn, int forced_run,
     for (int64_t l = lmin + 1; l <= 2 * lmin; ++l)
         if (load(l) < load(best)) best = l;
     // requantized output leaves by single bytes whatever the run, so shorter
-    // runs in more than one round may also balance the CUs (ResNet-18 layers
-    // 9 and 12 at batch 128: 12544 units in runs of 2 give some CUs 7 blocks
-    // and most 6; in runs of 1, 13 and 12)
-    if (rq)
+    // runs in more than one round may also balance the CUs (ResNet-18 layer 9
+    // at batch 128: 12544 units of 8 channels in runs of 2 give some CUs 7
+    // blocks and most 6; in runs of 1, 13 and 12; 55.9 -> 53.2 us).  Every run
+    // loads its pixels' words again, which 1x1 windows with 1-bit filters and
+    // many words do not cover (14x14x256 -> 256 A4W1 at batch 128: runs of 1
+    // 21.7 us, of 2 18.8; A2W1 11.3 and 11.3)
+    if (rq && !(s.kh == 1 && s.wbits == 1 && s.abits * ((s.c + 31) / 32) >= 32))
         for (int64_t l = lmin - 1; 2 * l >= lmin && l >= 1; --l)
             if (load(l) < load(best)) best = l;
     // 1x1 layers with few word pairs per result (A W words <= 16) are bound
