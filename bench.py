@@ -48,7 +48,9 @@ PROFILES = os.path.join(ROOT, "profiles")
 # their hash matches the one recorded with it
 CONV_SOURCES = ["paper_1810_11066_amd/csrc/" + f for f in (
     "bs_internal.h", "conv.hip", "conv_fast.h", "conv_fast_inst.hip",
-    "conv_pix.h", "conv_pix.hip", "conv_pix_inst.hip")]
+    "conv_pix.h", "conv_pix.hip", "conv_pix_inst.hip", "conv_tiled.h",
+    "conv_tiled.hip", "conv_tiled_inst.hip", "dense_rows.h",
+    "dense_rows.hip")]
 
 
 def popcount_roofline_tops(abits: int, wbits: int) -> float:
