@@ -107,8 +107,9 @@ def test_conv_encodings(oracle, bits):
     (64, 4), (65, 5), (130, 12), (63, 16), (64, 17), (200, 31), (128, 150),
     (4100, 150), (20000, 40)])
 def test_conv_tiles(oracle, npix, oc):
-    """Pixel groups and channel tiles at their edges, from one unit whose
-    steps are shared to grids that fill the chip with the widest tiles."""
+    """Pixel groups and channel tiles at their edges, in the 4-channel tiles
+    that these grids take, from one unit whose steps are shared to thousands
+    of units (test_wide_tiles has the wider ones)."""
     for abits, wbits in ((1, 1), (2, 2), (3, 3)):
         if npix * oc > 10 ** 5 and abits > 1:
             continue
@@ -190,3 +191,103 @@ def test_requant(oracle, oc, obits):
                              dev(wp.view(np.int32)), scale, obits, g.t)
         got = g.numpy().view(np.uint32)
         assert np.array_equal(got.reshape(want.shape), want)
+
+
+# n, h, w, c, oc, (kh, kw), abits, wbits, aenc, wenc, channels per tile: grids of
+# more than three waves a SIMD, units of 16 channels with a ragged last one
+WIDE = [
+    (32, 27, 27, 96, 150, (3, 3), 2, 1, U, B, 16),     # chunks of 3 words
+    (32, 27, 27, 17, 150, (3, 3), 1, 2, U, S, 16),     # 1 word
+    (32, 27, 27, 64, 150, (5, 5), 2, 2, S, U, 16),     # 2 words
+    (64, 27, 27, 130, 78, (3, 3), 1, 4, U, U, 16),     # 3 + 2 words
+    (32, 27, 27, 200, 150, (1, 3), 4, 1, U, U, 16),    # 4 + 3 words
+    (32, 27, 27, 96, 150, (3, 3), 2, 1, B, U, 16),     # SW pass
+    (32, 27, 27, 96, 150, (3, 3), 1, 2, B, B, 16),     # +-1 activations
+    (32, 27, 27, 70, 152, (3, 3), 1, 1, B, B, 16),     # XNOR, whole quads
+    (32, 27, 27, 96, 158, (3, 3), 2, 3, U, U, 8),
+    (32, 27, 27, 60, 158, (3, 3), 4, 2, B, S, 8),      # SW pass
+    (32, 27, 27, 96, 158, (2, 3), 5, 2, S, U, 8),      # 3 + 2 planes
+    (32, 27, 27, 96, 158, (3, 3), 3, 3, U, B, 4),      # four tiles to a unit
+    (32, 27, 27, 40, 160, (3, 1), 6, 5, B, B, 4),      # plane groups, SW passes
+]
+
+
+def wide(shape):
+    n, h, w, c, oc, (kh, kw), abits, wbits, aenc, wenc, _ = shape
+    say("wide tiles", shape)
+    p = bs.ConvParams(n, h, w, c, oc, kh, kw, 1, 1, kh // 2, kw // 2, abits,
+                      wbits, aenc, wenc)
+    gen = torch.Generator("cuda").manual_seed(c + oc + abits)
+    a = bs.pack(torch.randint(0, 1 << abits, (n, h, w, c), dtype=torch.uint8,
+                              device="cuda", generator=gen), abits)
+    wq = bs.pack(torch.randint(0, 1 << wbits, (oc, kh, kw, c),
+                               dtype=torch.uint8, device="cuda",
+                               generator=gen), wbits)
+    return p, a, wq
+
+
+def plain(call):
+    bs.bs_set_kernel_mode(1)
+    try:
+        call()
+    finally:
+        bs.bs_set_kernel_mode(0)
+
+
+@pytest.mark.parametrize("shape", WIDE, ids=lambda s: "C%d_A%d%sW%d%s" % (
+    s[10], s[6], "ubs"[s[8]], s[7], "ubs"[s[9]]))
+def test_wide_tiles(shape):
+    """The channel tiles of grids that fill the chip, int32 and requantized,
+    against the plain kernel."""
+    p, a, wq = wide(shape)
+    d = bs.bs_conv2d_describe(p)
+    assert d.startswith("conv_generic_kernel_tiled") and " of 16 channels " in d
+    assert ",C=%d" % shape[10] in d, d
+    oh, ow = bs.bs_conv2d_out_shape(p)
+    numel = p.n * oh * ow * p.oc
+    want = torch.empty(numel, dtype=torch.int32, device="cuda")
+    plain(lambda: bs.bs_conv2d(p, a, wq, want))
+    g = Guarded(numel)
+    bs.bs_conv2d(p, a, wq, g.t)
+    g.numpy()
+    assert torch.equal(g.t, want)
+    scale = 7.0 / float(want.abs().float().mean() * 2 + 1)
+    words = p.n * oh * ow * 3 * bs.words(p.oc)
+    want = torch.empty(words, dtype=torch.int32, device="cuda")
+    plain(lambda: bs.bs_conv2d_requant(p, a, wq, scale, 3, want))
+    g = Guarded(words)
+    bs.bs_conv2d_requant(p, a, wq, scale, 3, g.t)
+    g.numpy()
+    assert torch.equal(g.t, want)
+
+
+def test_batch_split():
+    """An int32 output past 2 GiB, and packed activations past it with
+    requantized output: several launches of the tiled kernel."""
+    p, a, wq = wide((130, 56, 56, 32, 1342, (1, 1), 1, 1, U, U, 16))
+    d = bs.bs_conv2d_describe(p)
+    assert d.startswith("conv_generic_kernel_tiled") and "batch split" in d
+    numel = 130 * 56 * 56 * 1342
+    want = torch.empty(numel, dtype=torch.int32, device="cuda")
+    plain(lambda: bs.bs_conv2d(p, a, wq, want))
+    g = Guarded(numel)
+    bs.bs_conv2d(p, a, wq, g.t)
+    torch.cuda.synchronize()
+    assert torch.equal(g.t, want)
+    assert bool((g.buf[:GUARD] == SENT32).all())
+    assert bool((g.buf[-GUARD:] == SENT32).all())
+    del g, want
+    # 7200 x 56 x 56 pixels of 96 bytes
+    n = 7200
+    p = bs.ConvParams(n, 56, 56, 96, 10, 1, 1, 1, 1, 0, 0, 8, 1, U, U)
+    a = torch.randint(-2 ** 31, 2 ** 31 - 1, (n, 56, 56, 8, 3),
+                      dtype=torch.int32, device="cuda")
+    wq = bs.pack(torch.randint(0, 2, (10, 1, 1, 96), dtype=torch.uint8,
+                               device="cuda"), 1)
+    say("batch split, requantized", n)
+    words = n * 56 * 56 * 2
+    want = torch.empty(words, dtype=torch.int32, device="cuda")
+    plain(lambda: bs.bs_conv2d_requant(p, a, wq, 3e-4, 2, want))
+    got = torch.full((words,), SENT32, dtype=torch.int32, device="cuda")
+    bs.bs_conv2d_requant(p, a, wq, 3e-4, 2, got)
+    assert torch.equal(got, want)
