@@ -314,7 +314,8 @@ int resident_blocks(pix::PixKernelFn fn, size_t lds) {
     return blocks;
 }
 
-// The kernel of a planned grid; int32_out: a plain call's int32 output.
+// The kernel of a planned grid (src: the activations' source; stored: a single
+// int32 output).
 //
 // The one for lone waves where no SIMD gets a second wave, i.e. a CU a second
 // block (blocks are one wave per SIMD).  On either side of the line, kernel
@@ -323,20 +324,23 @@ int resident_blocks(pix::PixKernelFn fn, size_t lds) {
 // 10.1; requantized 16x16x256 -> 256 A2W1 9.7 / 11.3 and 13.4 / 12.1.
 //
 // It also serves int32 results of few word pairs each, whose stores bound the
-// call: 64x56x56x32 -> 64 3x3 A1W1 (9 pairs) 14.4 / 17.2 us, 64x28x28x128 ->
-// 256 1x1 A2W1 (8 pairs) 11.9 / 13.1; at 18 pairs 64x56x56x32 -> 64 A2W1 21.4 /
-// 19.8, but where the pixel rows end within a 64-byte piece 32x28x28x32 -> 732
-// 29.3 / 33.1.  4-bit activations have 32 words of a pixel to 8 pairs and gain
-// from the other kernel (64x28x28x64 -> 256 1x1 A4W1 14.2 / 13.3 us).
+// call: 64x56x56x32 -> 64 3x3 A1W1 (9 pairs) 14.4 / 17.2 us (from codes 16.0 /
+// 17.9), 64x28x28x128 -> 256 1x1 A2W1 (8 pairs) 11.9 / 13.1; at 18 pairs
+// 64x56x56x32 -> 64 A2W1 21.4 / 19.8, but where the pixel rows end within a
+// 64-byte piece 32x28x28x32 -> 732 29.3 / 33.1 (from codes, 1x1 at stride 2, 256
+// channels, 10.8 / 13.3).  4-bit activations have 32 words of a pixel to 8 pairs
+// and gain from the other kernel (64x28x28x64 -> 256 1x1 A4W1 14.2 / 13.3 us), and
+// so do staged 1x1 windows with whole pieces (128x28x28x128 -> 256 at stride 2
+// from float32, A2W1, 10.1 / 9.9 us a pass).
 pix::PixKernelFn kernel_for_grid(const ConvShape& s, const pix::PixKernels& k,
-                                 const dim3& grid, bool int32_out) {
+                                 const dim3& grid, int src, bool stored) {
     static_assert(pix::kWavesPerBlock == 4, "one wave per SIMD and block");
     if ((int64_t)grid.x <= device_cus()) return k.alone;
     const int64_t pairs = (int64_t)s.kh * s.kw * ((s.c + 31) / 32) * s.abits *
                           s.wbits;
-    if (int32_out && s.abits <= 3 && pairs <= (s.oc % 16 ? 18 : 9))
-        return k.alone;
-    return k.fn;
+    const int few = s.oc % 16 ? 18
+                    : src == pix::kSrcPacked || s.kh > 1 ? 9 : 0;
+    return stored && s.abits <= 3 && pairs <= few ? k.alone : k.fn;
 }
 
 // Largest input region, in pixels, that a block of a staged launch packs
@@ -637,8 +641,8 @@ hipError_t launch_pix(const ConvShape& s, const pix::PixKernels& k,
         // kernels without a paired conv never read wts1
         const uint32_t* w1 = pair ? pair->wts1 : wts;
         const hipError_t e =
-            launch(kernel_for_grid(c, k, grid, !rq && !pair), grid,
-                   dim3(pix::kBlock), lds, st, a, wts, w1, o, g);
+            launch(kernel_for_grid(c, k, grid, pix::kSrcPacked, !rq && !pair),
+                   grid, dim3(pix::kBlock), lds, st, a, wts, w1, o, g);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -680,7 +684,7 @@ hipError_t launch_pix_staged(const ConvShape& s, const void* act, int src,
             static_cast<const uint8_t*>(act) + ch.n0 * in_img);
         int32_t* o = out + ch.n0 * out_img;
         const hipError_t e =
-            launch(kernel_for_grid(s, k, ch.grid, true), ch.grid,
+            launch(kernel_for_grid(s, k, ch.grid, src, true), ch.grid,
                    dim3(pix::kBlock), ch.lds, st, a, wts, wts, o, ch.g);
         if (e != hipSuccess) return e;
     }
@@ -785,7 +789,12 @@ bool plain_is_faster(const ConvShape& s) {
 // keeps mode 0 on it wherever it exists.
 Family choose(const ConvShape& s, const ConvOptions& opt,
               pix::PixKernels* pfn, pix::PlanInfo* info) {
-    const int mode = opt.mode;
+    const int mode = opt.mode, cus = device_cus();
+    // (products of few rows need no look at the pixel kernels if both bounds
+    // hold)
+    if (mode == 0 && opt.units_per_wave == 0 && rows::covers(s, cus, true) &&
+        rows::covers(s, cus, false))
+        return Family::kRows;
     if (mode == 0 || mode == 3)
         *pfn = pix_kernel_for(s, false, pix::kSrcPacked, info);
     if (mode == 3) return *pfn ? Family::kPixels : Family::kGeneric;
@@ -793,7 +802,7 @@ Family choose(const ConvShape& s, const ConvOptions& opt,
     if (mode != 0) return Family::kGeneric;
     if (*pfn && opt.units_per_wave > 0) return Family::kPixels;
     const bool pixel = *pfn && !tiled_is_faster(s, *info);
-    if (rows::covers(s, device_cus(), pixel)) return Family::kRows;
+    if (rows::covers(s, cus, pixel)) return Family::kRows;
     if (pixel) return Family::kPixels;
     if (!*pfn && channels_are_faster(s)) return Family::kChannels;
     if (!*pfn && plain_is_faster(s)) return Family::kGeneric;
@@ -973,7 +982,7 @@ int describe_conv_staged(const ConvShape& s, bool from_float,
                     from_float ? "float32" : "codes",
                     info.tb, info.cb, info.ocb, info.ts, grid.x, pix::kBlock,
                     lds, g.region_pixels, g.units, g.per_wave,
-                    kernel_for_grid(s, fn, grid, true) != fn.fn
+                    kernel_for_grid(s, fn, grid, src, true) != fn.fn
                         ? " lone waves" : "",
                     launches > 1 ? " (per launch; batch split)" : "");
 }
@@ -1011,7 +1020,8 @@ int describe_conv(const ConvShape& s, const ConvOptions& opt, char* buf,
                             s.abits, s.wbits, kenc, s.kh, s.sh, cw, info.tb,
                             info.cb, info.ocb, info.ts, grid.x, pix::kBlock,
                             lds, g.units, g.per_wave,
-                            kernel_for_grid(s, pfn, grid, true) != pfn.fn
+                            kernel_for_grid(s, pfn, grid, pix::kSrcPacked,
+                                            true) != pfn.fn
                                 ? " lone waves" : "",
                             launches > 1 ? " (per launch; batch split)" : "");
         }

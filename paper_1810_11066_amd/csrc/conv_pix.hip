@@ -45,8 +45,10 @@ PixKernelFn pick_one(int a, int w, int ae, int we, int k, int s, int cw,
 
 PixKernels pick(int a, int w, int ae, int we, int k, int s, int cw, bool req,
                 int src, bool dual, PlanInfo* info) {
-    return {pick_one<false>(a, w, ae, we, k, s, cw, req, src, dual, info),
-            pick_one<true>(a, w, ae, we, k, s, cw, req, src, dual, info)};
+    const PixKernelFn fn =
+        pick_one<false>(a, w, ae, we, k, s, cw, req, src, dual, info);
+    if (!fn) return {};
+    return {fn, pick_one<true>(a, w, ae, we, k, s, cw, req, src, dual, info)};
 }
 
 }  // namespace pix

@@ -56,6 +56,18 @@ def test_store_bound_results(c, oc, k, abits, wbits, lone):
     assert d.endswith(" lone waves") == lone, d
 
 
+@pytest.mark.parametrize("c,oc,k,lone", [
+    (32, 64, 3, True), (32, 732, 3, True), (128, 256, 1, False),
+    (128, 732, 1, True)])
+def test_store_bound_staged(c, oc, k, lone):
+    bs.bs_set_units_per_wave(1)
+    p = conv(64, 28, 28, c, oc, k, 1, 2 if k == 1 else 1, 1)
+    for describe in ([bs.bs_conv2d_codes_describe] +
+                     [bs.bs_conv2d_quantized_describe] * (k == 1)):
+        d = describe(p)
+        assert d.endswith(" lone waves") == lone, d
+
+
 @pytest.mark.parametrize("m,k,n,abits,wbits,rows", [
     # waves per SIMD of 4 rows x 4 columns (A W <= 4) or of one row, against
     # the pixel kernel: 3 (8 of one row), any up to 8 (10) rows
