@@ -97,11 +97,17 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     g.div_kw.init((uint32_t)s.kw);
 
     // The tile: the widest one, unless a quarter of its channels would be
-    // padding; narrower units, then waves sharing a unit's steps, then
-    // 4-channel tiles, until there are 3 waves for every SIMD (each narrowing
-    // repeats a wave's set-up, about 250 vector instructions).
+    // padding; narrower units, then waves sharing a unit's steps, until there
+    // are 4 waves for every SIMD (each narrowing repeats a wave's set-up,
+    // about 250 vector instructions).  Split / whole units between 3 and 4
+    // waves a SIMD: 44x20x20x192 -> 192 3x3 A2W1 32.4 / 37.6 us, A2W2 55.1 / 61.4,
+    // A3W3 108 / 124; 178x14x14x64 -> 96 5x5 33.4 / 36.7; 583x9x9x352 -> 70 A1W2
+    // 60.1 / 64.2; 29x27x27x96 -> 150 A2W1 20.6 / 22.4, of 32 images A1W2 26.4 /
+    // 25.0.  4-channel tiles load each word four times as often and only help
+    // below 3 waves a SIMD (at 3.2, 4 / 16 channels: 45x14x14x64 -> 96 5x5 A2W1
+    // 15.9 / 13.1 us, A1W2 17.6 / 14.1, 129x9x9x352 -> 70 18.9 / 19.6).
     const int64_t groups = ceil_div(g.npix, 64);
-    const int64_t want = (int64_t)cus * 4 * 3;
+    const int64_t want = (int64_t)cus * 4 * 4, few = (int64_t)cus * 4 * 3;
     const int least = rq ? 8 : 4;      // a packed byte is 8 channels
     pl.c = max_channels(pl.a, pl.w);
     if (4 * (int64_t)s.oc < 3 * ceil_div(s.oc, pl.c) * pl.c) pl.c = 4;
@@ -114,9 +120,9 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     while (waves() < want && cols > pl.c && cols > least) cols /= 2;
     while (waves() < want && g.ks_log2 < 2 && g.nsteps >= 4 << g.ks_log2)
         ++g.ks_log2;
-    while (waves() < want && pl.c > 4) {
+    while (waves() < few && pl.c > 4) {
         pl.c = 4;
-        while (waves() < want && cols > pl.c && cols > least) cols /= 2;
+        while (waves() < few && cols > pl.c && cols > least) cols /= 2;
     }
     g.unit_cols = cols;
     g.nsub = cols / pl.c;

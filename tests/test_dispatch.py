@@ -68,6 +68,20 @@ def test_store_bound_staged(c, oc, k, lone):
         assert d.endswith(" lone waves") == lone, d
 
 
+def test_waves_of_a_tiled_unit():
+    """Units of 16 channels: split over waves until there are 4 waves for
+    every SIMD, in 4-channel tiles below 3."""
+    for n, plan in ((48, "C=16> A=2 W=1 bipolar grid=1368 block=256 units=5470 "
+                         "of 16 channels waves_per_unit=1"),
+                    (32, "C=16> A=2 W=1 bipolar grid=1825 block=256 units=3650 "
+                         "of 16 channels waves_per_unit=2"),
+                    (7, "C=16> A=2 W=1 bipolar grid=800 block=256 units=800 "
+                        "of 16 channels waves_per_unit=4"),
+                    (6, "C=4> ")):
+        p = conv(n, 27, 27, 96, 150, 3, 1, 2, 1, U, B)
+        assert plan in bs.bs_conv2d_describe(p), bs.bs_conv2d_describe(p)
+
+
 @pytest.mark.parametrize("m,k,n,abits,wbits,rows", [
     # waves per SIMD of 4 rows x 4 columns (A W <= 4) or of one row, against
     # the pixel kernel: 3 (8 of one row), any up to 8 (10) rows

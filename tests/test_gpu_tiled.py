@@ -194,21 +194,21 @@ def test_requant(oracle, oc, obits):
 
 
 # n, h, w, c, oc, (kh, kw), abits, wbits, aenc, wenc, channels per tile: grids of
-# more than three waves a SIMD, units of 16 channels with a ragged last one
+# more than four waves a SIMD, units of 16 channels with a ragged last one
 WIDE = [
-    (32, 27, 27, 96, 150, (3, 3), 2, 1, U, B, 16),     # chunks of 3 words
-    (32, 27, 27, 17, 150, (3, 3), 1, 2, U, S, 16),     # 1 word
-    (32, 27, 27, 64, 150, (5, 5), 2, 2, S, U, 16),     # 2 words
-    (64, 27, 27, 130, 78, (3, 3), 1, 4, U, U, 16),     # 3 + 2 words
-    (32, 27, 27, 200, 150, (1, 3), 4, 1, U, U, 16),    # 4 + 3 words
-    (32, 27, 27, 96, 150, (3, 3), 2, 1, B, U, 16),     # SW pass
-    (32, 27, 27, 96, 150, (3, 3), 1, 2, B, B, 16),     # +-1 activations
-    (32, 27, 27, 70, 152, (3, 3), 1, 1, B, B, 16),     # XNOR, whole quads
-    (32, 27, 27, 96, 158, (3, 3), 2, 3, U, U, 8),
-    (32, 27, 27, 60, 158, (3, 3), 4, 2, B, S, 8),      # SW pass
-    (32, 27, 27, 96, 158, (2, 3), 5, 2, S, U, 8),      # 3 + 2 planes
-    (32, 27, 27, 96, 158, (3, 3), 3, 3, U, B, 4),      # four tiles to a unit
-    (32, 27, 27, 40, 160, (3, 1), 6, 5, B, B, 4),      # plane groups, SW passes
+    (48, 27, 27, 96, 150, (3, 3), 2, 1, U, B, 16),     # chunks of 3 words
+    (48, 27, 27, 17, 150, (3, 3), 1, 2, U, S, 16),     # 1 word
+    (48, 27, 27, 64, 150, (5, 5), 2, 2, S, U, 16),     # 2 words
+    (96, 27, 27, 130, 78, (3, 3), 1, 4, U, U, 16),     # 3 + 2 words
+    (48, 27, 27, 200, 150, (1, 3), 4, 1, U, U, 16),    # 4 + 3 words
+    (48, 27, 27, 96, 150, (3, 3), 2, 1, B, U, 16),     # SW pass
+    (48, 27, 27, 96, 150, (3, 3), 1, 2, B, B, 16),     # +-1 activations
+    (48, 27, 27, 70, 152, (3, 3), 1, 1, B, B, 16),     # XNOR, whole quads
+    (48, 27, 27, 96, 158, (3, 3), 2, 3, U, U, 8),
+    (48, 27, 27, 60, 158, (3, 3), 4, 2, B, S, 8),      # SW pass
+    (48, 27, 27, 96, 158, (2, 3), 5, 2, S, U, 8),      # 3 + 2 planes
+    (48, 27, 27, 96, 158, (3, 3), 3, 3, U, B, 4),      # four tiles to a unit
+    (48, 27, 27, 40, 160, (3, 1), 6, 5, B, B, 4),      # plane groups, SW passes
 ]
 
 
