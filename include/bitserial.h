@@ -336,6 +336,8 @@ bs_status bs_set_kernel_mode(int mode);
  * (for bs_conv2d_quantized with strided 1x1 windows, lengthened until at
  * most two workgroups share a group of 64 output pixels, while the grid
  * keeps a workgroup for at least every other compute unit).
+ * While it is set, kernel mode 0 takes the pixels-on-lanes kernel for every
+ * shape that has one, also where another kernel would be chosen.
  * Results do not depend on it; it exists for tests of the run boundaries and
  * for tuning.  Errors: BS_ERR_INVALID_ARG for units < 0. */
 bs_status bs_set_units_per_wave(int units);
