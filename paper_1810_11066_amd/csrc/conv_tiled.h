@@ -22,8 +22,8 @@
 //
 // Measured against what served these shapes before (one output per thread):
 // 32 x 27 x 27 x 96 -> 150 channels, 3x3, A2 x bipolar W1, quantize+pack
-// included: 290 -> 27.5 us a pass; 100 x 784 x 1000 product, A2W2: 64.6 ->
-// 13.6 us (of which the host takes most).
+// included: 290 -> 25.3 us a pass; 100 x 784 x 1000 product, A2W2: 64.6 ->
+// 14.2 us (of which the host takes most).
 //
 // Filter words come through s_buffer_load, whose range check makes the last
 // channel tile and the over-read of a 3-word chunk safe without clamping.
