@@ -97,17 +97,24 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
     g.div_kw.init((uint32_t)s.kw);
 
     // The tile: the widest one, unless a quarter of its channels would be
-    // padding; narrower units, then waves sharing a unit's steps, until there
-    // are 4 waves for every SIMD (each narrowing repeats a wave's set-up,
-    // about 250 vector instructions).  Split / whole units between 3 and 4
-    // waves a SIMD: 44x20x20x192 -> 192 3x3 A2W1 32.4 / 37.6 us, A2W2 55.1 / 61.4,
-    // A3W3 108 / 124; 178x14x14x64 -> 96 5x5 33.4 / 36.7; 583x9x9x352 -> 70 A1W2
-    // 60.1 / 64.2; 29x27x27x96 -> 150 A2W1 20.6 / 22.4, of 32 images A1W2 26.4 /
-    // 25.0.  4-channel tiles load each word four times as often and only help
-    // below 3 waves a SIMD (at 3.2, 4 / 16 channels: 45x14x14x64 -> 96 5x5 A2W1
-    // 15.9 / 13.1 us, A1W2 17.6 / 14.1, 129x9x9x352 -> 70 18.9 / 19.6).
+    // padding.  Then more waves, each of which repeats a wave's set-up (about
+    // 250 vector instructions): narrower units until there are 4 waves for every
+    // SIMD; waves sharing a unit's steps, two until there are 4, or four until
+    // there are 3.5, or either until there are 3 where a unit has less than 12
+    // steps; and 4-channel tiles, which load each word four times as often,
+    // until there are 3.
+    //
+    // Whole / shared units at 3 to 3.6 waves a SIMD: 44x20x20x192 -> 192 3x3 (18
+    // steps) A2W1 37.6 / 32.4 us, A2W2 61.4 / 55.1; 178x14x14x64 -> 96 5x5 (25)
+    // 36.7 / 33.4; 583x9x9x352 -> 70 (27) A1W2 64.2 / 60.1.  Over 233 random shapes,
+    // rate shared / whole: two waves, 24 steps and more 1.04 to 1.19, less than 6
+    // 0.88 to 0.99; four waves, 12 and more 1.00 to 1.13 up to 3.5 waves a SIMD,
+    // 0.98 to 1.01 above, less than 12 0.87 to 0.98; narrower units 1.02 to 1.19.
+    // 4 / 16 channels at 3.2 waves: 45x14x14x64 -> 96 5x5 A2W1 15.9 / 13.1 us, A1W2
+    // 17.6 / 14.1, 129x9x9x352 -> 70 18.9 / 19.6.
     const int64_t groups = ceil_div(g.npix, 64);
-    const int64_t want = (int64_t)cus * 4 * 4, few = (int64_t)cus * 4 * 3;
+    const int64_t simds = (int64_t)cus * 4;
+    const int64_t want = simds * 4, few = simds * 3;
     const int least = rq ? 8 : 4;      // a packed byte is 8 channels
     pl.c = max_channels(pl.a, pl.w);
     if (4 * (int64_t)s.oc < 3 * ceil_div(s.oc, pl.c) * pl.c) pl.c = 4;
@@ -118,7 +125,9 @@ Plan make_plan(const ConvShape& s, const Requant* rq, int pix_step,
         cols /= 2;
     auto waves = [&]() { return groups * ceil_div(s.oc, cols) << g.ks_log2; };
     while (waves() < want && cols > pl.c && cols > least) cols /= 2;
-    while (waves() < want && g.ks_log2 < 2 && g.nsteps >= 4 << g.ks_log2)
+    while (g.ks_log2 < 2 && g.nsteps >= 4 << g.ks_log2 &&
+           waves() < (g.nsteps < 12 ? few
+                      : g.ks_log2 == 0 ? want : simds * 7 / 2))
         ++g.ks_log2;
     while (waves() < few && pl.c > 4) {
         pl.c = 4;
