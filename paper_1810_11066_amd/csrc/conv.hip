@@ -331,15 +331,20 @@ int resident_blocks(pix::PixKernelFn fn, size_t lds) {
 // channels, 10.8 / 13.3).  4-bit activations have 32 words of a pixel to 8 pairs
 // and gain from the other kernel (64x28x28x64 -> 256 1x1 A4W1 14.2 / 13.3 us), and
 // so do staged 1x1 windows with whole pieces (128x28x28x128 -> 256 at stride 2
-// from float32, A2W1, 10.1 / 9.9 us a pass).
+// from float32, A2W1, 10.1 / 9.9 us a pass), several filter planes with whole
+// pieces (44x35x33x10 -> 768 1x1 A3W3 36.9 / 34.0), and ragged rows of several
+// filter planes with one activation plane or one word (9x33x27x10 -> 724 3x3
+// A1W2 11.9 / 11.2, 32x28x28x32 -> 732 1x1 A3W3 20.3 / 19.1).
 pix::PixKernelFn kernel_for_grid(const ConvShape& s, const pix::PixKernels& k,
                                  const dim3& grid, int src, bool stored) {
     static_assert(pix::kWavesPerBlock == 4, "one wave per SIMD and block");
     if ((int64_t)grid.x <= device_cus()) return k.alone;
-    const int64_t pairs = (int64_t)s.kh * s.kw * ((s.c + 31) / 32) * s.abits *
-                          s.wbits;
-    const int few = s.oc % 16 ? 18
-                    : src == pix::kSrcPacked || s.kh > 1 ? 9 : 0;
+    const int64_t red = (int64_t)s.kh * s.kw * ((s.c + 31) / 32);
+    const int64_t pairs = red * s.abits * s.wbits;
+    const int few = s.oc % 16
+                        ? (s.wbits == 1 || (s.abits > 1 && red > 1) ? 18 : 0)
+                    : s.wbits == 1 && (src == pix::kSrcPacked || s.kh > 1) ? 9
+                                                                       : 0;
     return stored && s.abits <= 3 && pairs <= few ? k.alone : k.fn;
 }
 
@@ -706,10 +711,12 @@ enum class Family { kPixels, kChannels, kTiled, kRows, kGeneric };
 // 43.9 / 27.2 but A2W1 9.7 / 10.8, A4W1 17.0 / 20.3; 640 units A2W2 13.9 / 15.5,
 // A4W4 43.8 / 37.0; 256 units A2W1 9.6 / 7.3, A4W1 16.6 / 11.7), or the words are
 // few (k = 1024, 512 units, A2W1 4.6 / 4.2).  One bit on both sides gains up
-// to 1 unit per CU (512 units 6.4 / 6.7 us, 128 units 6.1 / 5.8), short
-// reductions nowhere (14x14x512 -> 512 1x1, 512 units: A2W2 3.9 / 4.5).  Problems
-// of fewer than 16 units stay with the pixel kernel, and so do those above the
-// lines (896 units of 3x3 A4W4 48.3 / 38.3).
+// to 1 unit per CU (512 units 6.4 / 6.7 us, 128 units 6.1 / 5.8), with bipolar
+// filters or 1x1 windows to 2 (12x4x37x512 -> 64 3x3, 448 units, 7.1 / 6.1; k =
+// 4096, 512 units, 6.5 / 6.0, 640 units 6.6 / 8.1), short reductions nowhere
+// (14x14x512 -> 512 1x1, 512 units: A2W2 3.9 / 4.5).  Problems of fewer than 16
+// units stay with the pixel kernel, and so do those above the lines (896 units
+// of 3x3 A4W4 48.3 / 38.3).
 //
 // One unit per wave in a full round (12 to 28 units per CU) with multi-bit
 // activations and 1-bit filters: a wave then loads A words per popcount chain
@@ -732,7 +739,8 @@ bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
     const int red = taps * ((s.c + 31) / 32);       // words per plane
     int most = 0;                                   // units per CU
     if (red < 32 || a * red < 64) most = 0;
-    else if (aw == 1) most = 1;
+    else if (aw == 1)
+        most = taps == 1 || (s.aenc == kUnipolar && s.wenc == kBipolar) ? 2 : 1;
     else if (taps == 1 && s.wbits == 1) most = a * red <= 128 ? 2 : 1;
     else if (taps == 1) most = aw >= 16 ? 3 : 2;
     else most = a == 1 && red < 128 ? 1 : 3;
@@ -768,7 +776,9 @@ bool channels_are_faster(const ConvShape& s) {
 }
 
 // One output per thread, for one word per plane while there are at most 3 waves
-// of outputs per SIMD (2 above 9 bits a pair).  Plain / tiled: 64 Ki outputs
+// of outputs per SIMD (2 above 9 bits a pair), except with 8-bit filters, whose
+// planes fill the tiled kernel's groups (72000 outputs A1W8 5.6 / 4.5, A4W8 10.8 /
+// 6.1 us).  Plain / tiled: 64 Ki outputs
 // A1W1 2.5 / 3.0 us, A4W4 4.0 / 4.3, A5W5 4.8 / 7.4, A8W8 10.2 / 8.8; 128 Ki A1W1
 // 2.6 / 3.1, A3W3 3.5 / 3.9, A4W4 4.6 / 4.4; 158 Ki A2W2 3.3 / 3.9; 256 Ki A2W2
 // 3.6 / 3.6, A3W3 4.3 / 4.0.  At 2 words the two are within 0.4 us up to 64 Ki
@@ -776,7 +786,7 @@ bool channels_are_faster(const ConvShape& s) {
 // serves them.
 bool plain_is_faster(const ConvShape& s) {
     const int aw = s.abits * s.wbits;
-    return (int64_t)s.kh * s.kw * ((s.c + 31) / 32) == 1 && aw < 64 &&
+    return (int64_t)s.kh * s.kw * ((s.c + 31) / 32) == 1 && s.wbits < 8 &&
            (int64_t)s.n * s.oh * s.ow * s.oc <=
                (aw <= 9 ? 768 : 512) * (int64_t)device_cus();
 }

@@ -1,5 +1,7 @@
 """The kernel each rule of the dispatch picks, on both sides of its lines, by
 the describe calls (host-side planning for 256 compute units, no GPU)."""
+import re
+
 import pytest
 
 from paper_1810_11066_amd import bitserial as bs
@@ -48,6 +50,10 @@ def test_lone_waves():
     (64, 732, 3, 2, 1, False),     # 36
     (128, 256, 1, 2, 1, True),     # 8
     (64, 256, 1, 4, 1, False),     # 8, 4-bit activations
+    (32, 768, 1, 3, 3, False),     # 9, several filter planes
+    (32, 724, 3, 1, 2, False),     # 18, of one activation plane
+    (64, 732, 1, 3, 3, True),      # 18, of three
+    (32, 732, 1, 3, 3, False),     # 9, of three and one word
 ])
 def test_store_bound_results(c, oc, k, abits, wbits, lone):
     bs.bs_set_units_per_wave(1)
@@ -68,18 +74,27 @@ def test_store_bound_staged(c, oc, k, lone):
         assert d.endswith(" lone waves") == lone, d
 
 
-def test_waves_of_a_tiled_unit():
-    """Units of 16 channels: split over waves until there are 4 waves for
-    every SIMD, in 4-channel tiles below 3."""
-    for n, plan in ((48, "C=16> A=2 W=1 bipolar grid=1368 block=256 units=5470 "
-                         "of 16 channels waves_per_unit=1"),
-                    (32, "C=16> A=2 W=1 bipolar grid=1825 block=256 units=3650 "
-                         "of 16 channels waves_per_unit=2"),
-                    (7, "C=16> A=2 W=1 bipolar grid=800 block=256 units=800 "
-                        "of 16 channels waves_per_unit=4"),
-                    (6, "C=4> ")):
-        p = conv(n, 27, 27, 96, 150, 3, 1, 2, 1, U, B)
-        assert plan in bs.bs_conv2d_describe(p), bs.bs_conv2d_describe(p)
+@pytest.mark.parametrize("n,h,c,oc,k,abits,wbits,plan", [
+    # 9 steps: waves share a unit's until there are 3 for every SIMD
+    (48, 27, 96, 150, 3, 2, 1, "C=16> units=5470 of 16 waves=1"),
+    (29, 27, 96, 150, 3, 2, 1, "C=16> units=3310 of 16 waves=1"),
+    (26, 27, 96, 150, 3, 2, 1, "C=16> units=2970 of 16 waves=2"),
+    # 18 steps: two until there are 4, four until there are 3.5
+    (49, 20, 192, 192, 3, 2, 1, "C=16> units=3684 of 16 waves=2"),
+    (55, 20, 192, 192, 3, 2, 1, "C=16> units=4128 of 16 waves=1"),
+    (23, 20, 192, 192, 3, 2, 1, "C=16> units=1728 of 16 waves=4"),
+    (25, 20, 192, 192, 3, 2, 1, "C=16> units=1884 of 16 waves=2"),
+    # narrower units until there are 4
+    (44, 20, 192, 192, 3, 3, 3, "C=4> units=6600 of 8 waves=1"),
+    # 4-channel tiles below 3
+    (7, 27, 96, 150, 3, 2, 1, "C=16> units=800 of 16 waves=4"),
+    (6, 27, 96, 150, 3, 2, 1, "C=4> units=1311 of 8 waves=4")])
+def test_waves_of_a_tiled_unit(n, h, c, oc, k, abits, wbits, plan):
+    d = bs.bs_conv2d_describe(conv(n, h, h, c, oc, k, 1, abits, wbits, U, B))
+    assert d.startswith("conv_generic_kernel_tiled"), d
+    got = re.search(r"(C=\d+>).* (units=\d+ of \d+) channels "
+                    r"waves_per_unit=(\d)", d)
+    assert "%s %s waves=%s" % got.groups() == plan, d
 
 
 @pytest.mark.parametrize("m,k,n,abits,wbits,rows", [
@@ -118,10 +133,14 @@ def test_few_rows(m, k, n, abits, wbits, rows):
     # few units of 64 pixels x 4 channels
     (conv(1, 7, 7, 512, 512, 3, 1, 1, 1), True),          # 128
     (conv(4, 7, 7, 512, 512, 3, 1, 1, 1), False),         # 512
+    (conv(4, 7, 7, 512, 512, 3, 1, 1, 1, U, B), True),
+    (conv(6, 7, 7, 512, 512, 3, 1, 1, 1, U, B), False),   # 640
     (conv(6, 7, 7, 512, 512, 3, 1, 2, 1), True),          # 640
     (conv(8, 7, 7, 512, 512, 3, 1, 2, 1), False),         # 896
     (conv(1, 14, 14, 512, 512, 1, 1, 2, 2), False),       # 16 words
-    (dense(256, 4096, 512, 2, 1), False),                 # 512, products
+    (dense(256, 4096, 512, 1, 1), True),                  # 512, products
+    (dense(320, 4096, 512, 1, 1), False),                 # 640
+    (dense(256, 4096, 512, 2, 1), False),                 # 512
     (dense(256, 4096, 256, 2, 1), True),                  # 256
     (dense(256, 1024, 512, 2, 1), True),                  # 512, 32 words
     (dense(256, 4096, 512, 2, 2), True),
@@ -157,7 +176,8 @@ def test_long_reductions(p, tiled):
     (dense(3073, 32, 64, 2, 2, S, U), "conv_generic_kernel_tiled"),
     (dense(2048, 32, 64, 4, 4, S, U), "conv_generic_kernel A"),
     (dense(2049, 32, 64, 4, 4, S, U), "conv_generic_kernel_tiled"),
-    (dense(64, 32, 64, 8, 8, S, U), "conv_generic_kernel_tiled"),
+    (dense(64, 32, 64, 4, 8, S, U), "conv_generic_kernel_tiled"),
+    (dense(64, 32, 64, 8, 7, S, U), "conv_generic_kernel A"),
     (dense(64, 64, 64, 2, 2, S, U), "conv_generic_kernel_tiled")])
 def test_short_reductions(p, kernel):
     assert bs.bs_conv2d_describe(p).startswith(kernel)
