@@ -757,22 +757,22 @@ bool tiled_is_faster(const ConvShape& s, const pix::PlanInfo& info) {
 // wave (about 250 vector instructions) outweighs the products.
 //
 // Channels on lanes, up to 4 words per plane: one or two bits a pair of codes,
-// until its 64-channel blocks pass 64 Ki lanes per CU (16 Ki where most of a
-// block's lanes idle); 2 words also for blocks without idle lanes, whatever
-// their number, except at 3 to 8 bits a pair.  Channels-on-lanes / tiled: 128 Ki
+// until its 64-channel blocks pass 16 Ki lanes per CU (4 Ki where most of a
+// block's lanes idle); 2 words and blocks without idle lanes up to 32 Ki
+// per CU, except at 3 to 8 bits a pair.  Channels-on-lanes / tiled: 128 Ki
 // outputs of 66 channels, 2 words, A2W1 2.5 / 3.3 us, 2 Mi 5.2 / 7.0, 6 Mi 10.7
 // / 11.0; 4 words A1W1 2 Mi 6.5 / 7.1, 6 Mi 13.9 / 10.4; 10 channels, 2 words,
-// A2W1 128 Ki 2.7 / 3.3, 512 Ki 4.1 / 4.0; 402 channels, 2 words, 6 Mi A4W4 30.4
-// / 34.8, A2W2 14.7 / 13.4.
+// A2W1 128 Ki 2.7 / 3.3, 512 Ki 4.1 / 4.0; 402 channels, 2 words, 6 Mi A2W1 8.8 /
+// 10.2, A4W4 30.4 / 34.8, A2W2 14.7 / 13.4; 849 channels, 22 Mi A2W1 31.5 / 24.4.
 bool channels_are_faster(const ConvShape& s) {
     const int64_t red = (int64_t)s.kh * s.kw * ((s.c + 31) / 32);
     if (red > 4 || !conv_has_fast_path(s)) return false;
     const int64_t aw = (int64_t)s.abits * s.wbits;
     const int64_t lanes = ((int64_t)s.oc + 63) / 64 * 64;
     const bool full = 9 * (int64_t)s.oc >= 8 * lanes;
-    if (red <= 2 && full && (aw <= 2 || aw >= 9)) return true;
-    return aw <= 2 && (int64_t)s.n * s.oh * s.ow * lanes <=
-                          (s.oc >= 32 ? 16384 : 4096) * (int64_t)device_cus();
+    const int64_t per_cu = (int64_t)s.n * s.oh * s.ow * lanes / device_cus();
+    if (red <= 2 && full && (aw <= 2 || aw >= 9)) return per_cu <= 32768;
+    return aw <= 2 && per_cu <= (s.oc >= 32 ? 16384 : 4096);
 }
 
 // One output per thread, for one word per plane while there are at most 3 waves

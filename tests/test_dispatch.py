@@ -162,10 +162,12 @@ def test_long_reductions(p, tiled):
 @pytest.mark.parametrize("p,kernel", [
     # 2 and 4 words per plane: channels on lanes
     (dense(1900, 64, 66, 2, 1, U, B), "conv_ocl_kernel"),
-    (dense(32768, 64, 66, 2, 1, U, B), "conv_ocl_kernel"),    # 64 Ki lanes a CU
-    (dense(32769, 64, 66, 2, 1, U, B), "conv_generic_kernel_tiled"),
+    (dense(32768, 64, 66, 2, 1, U, B), "conv_ocl_kernel"),    # 16 Ki lanes a CU
+    (dense(32770, 64, 66, 2, 1, U, B), "conv_generic_kernel_tiled"),
     (dense(16384, 64, 10, 2, 1, U, B), "conv_ocl_kernel"),
-    (dense(16385, 64, 10, 2, 1, U, B), "conv_generic_kernel_tiled"),
+    (dense(16388, 64, 10, 2, 1, U, B), "conv_generic_kernel_tiled"),
+    (dense(9362, 64, 849, 2, 1, U, B), "conv_ocl_kernel"),    # 32 Ki
+    (dense(9364, 64, 849, 2, 1, U, B), "conv_generic_kernel_tiled"),
     (dense(15000, 64, 402, 4, 4, U, B), "conv_ocl_kernel"),
     (dense(15000, 64, 402, 2, 2, U, B), "conv_generic_kernel_tiled"),
     (dense(1900, 64, 66, 4, 4, U, B), "conv_generic_kernel_tiled"),
