@@ -22,7 +22,7 @@
 //
 // Measured against what served these shapes before (one output per thread):
 // 32 x 27 x 27 x 96 -> 150 channels, 3x3, A2 x bipolar W1, quantize+pack
-// included: 290 -> 25.3 us a pass; 100 x 784 x 1000 product, A2W2: 64.6 ->
+// included: 290 -> 25.7 us a pass; 100 x 784 x 1000 product, A2W2: 64.6 ->
 // 14.2 us (of which the host takes most).
 //
 // Filter words come through s_buffer_load, whose range check makes the last
